@@ -2267,26 +2267,22 @@ __global__ __launch_bounds__(kQrgThreads) void k_qrg(QrArgs q) {
 }
 
 // ---------------------------------------------------------------------------
-// Blocked Householder QR on FP64 MFMA tiles, one workgroup of NW waves per
-// item.  The panel stays in registers as 16x16 tiles in the MFMA accumulator
-// layout (register s of lane l holds row 4s + l/16, column l%16 of its tile);
-// wave w owns row tiles w, w + NW, ... of every column tile.  Columns are
-// factorised in blocks of 16 as in dgeqrf.  Inside a block, step k
-// broadcasts column k along each 16-lane row (DPP row_newbcast) and forms,
-// in one pass and one cross-wave sum, x^T a_c for every column c (x = column
-// k below the diagonal) and the row-k entries a_kc; column k's own entries
-// give sigma^2 and alpha for dlarfg, and w_c = a_kc + scal x^T a_c gives the
-// dlarf update of the block's later columns.  The block reflector
-// I - V T V^T (T from dlarft) is then applied to the columns on the right on
-// MFMA (W = V^T A, A -= V T^T W).  Q is formed backwards over the blocks as
-// in dorgqr: the block reflector updates the columns on the right, and the
-// block's own columns are E - V (T V_top^T), E the unit columns, both on
-// MFMA.  The reflectors are those of the unblocked algorithm (dgeqr2); only
-// the rounding order of sums and updates differs.  Cross-wave sums are taken
-// in a fixed order that every wave repeats, so all waves hold the same bits.
+// Blocked Householder QR on FP64 MFMA tiles, workgroups of NW waves.  A column
+// tile (16 columns, up to 16 NW RT rows) stays in registers as 16x16 tiles in
+// the MFMA accumulator layout (register s of lane (lr, lc) holds row 4s + lr,
+// column lc of its tile); wave w owns row tiles w, w + NW, ....  Columns are
+// factorised in blocks of 16 as in dgeqrf (qm_factor below), and the block
+// reflector I - V T V^T (T from dlarft) is applied to the columns on the
+// right on MFMA (W = V^T A, A -= V T^T W).  Q is formed backwards over the
+// blocks as in dorgqr: the block reflector updates the columns on the right,
+// and the block's own columns are E - V (T V_top^T), E the unit columns.  The
+// reflectors are those of the unblocked algorithm (dgeqr2); only the rounding
+// order of sums and updates differs.  Cross-wave sums are taken in a fixed
+// order that every wave repeats, so all waves hold the same bits.
+//
 // ---------------------------------------------------------------------------
 
-constexpr int kQmRowCap = 768;        // rows held by one workgroup, at most
+constexpr int kQmRowCap = 768;        // rows held by one k_qrm workgroup, at most
 // V column c of the block starts at c * kQmVs + (c & 14) doubles: with the
 // column stride 16 (mod 32) and that shift, both the per-lane column walk
 // (lane (lr, lc) reads column lc, rows 4s + lr) and the MFMA operand read
@@ -2317,35 +2313,11 @@ __device__ __forceinline__ int cl_index(int i, int j) {  // accumulator slot of 
   return (i >> 2) * 64 + (i & 3) * 16 + j;
 }
 
-template <int CTRL, int N>
-__device__ __forceinline__ void newbcast_all(double *d, const double *x) {
-#pragma unroll
-  for (int i = 0; i < N; ++i)
-    d[i] = __longlong_as_double(
-        __builtin_amdgcn_mov_dpp(__double_as_longlong(x[i]), CTRL, 0xf, 0xf, true));
-}
-
-// d[i] = x[i] of lane `src` of the same 16-lane row (64-bit row_newbcast)
-template <int N>
-__device__ __forceinline__ void row_bcast(double *d, const double *x, int src) {
-  switch (src) {
-    case 0: newbcast_all<0x150, N>(d, x); break;
-    case 1: newbcast_all<0x151, N>(d, x); break;
-    case 2: newbcast_all<0x152, N>(d, x); break;
-    case 3: newbcast_all<0x153, N>(d, x); break;
-    case 4: newbcast_all<0x154, N>(d, x); break;
-    case 5: newbcast_all<0x155, N>(d, x); break;
-    case 6: newbcast_all<0x156, N>(d, x); break;
-    case 7: newbcast_all<0x157, N>(d, x); break;
-    case 8: newbcast_all<0x158, N>(d, x); break;
-    case 9: newbcast_all<0x159, N>(d, x); break;
-    case 10: newbcast_all<0x15A, N>(d, x); break;
-    case 11: newbcast_all<0x15B, N>(d, x); break;
-    case 12: newbcast_all<0x15C, N>(d, x); break;
-    case 13: newbcast_all<0x15D, N>(d, x); break;
-    case 14: newbcast_all<0x15E, N>(d, x); break;
-    default: newbcast_all<0x15F, N>(d, x); break;
-  }
+// x of lane SRC of the same 16-lane row (64-bit row_newbcast)
+template <int SRC>
+__device__ __forceinline__ double row_bcast(double x) {
+  return __longlong_as_double(
+      __builtin_amdgcn_mov_dpp(__double_as_longlong(x), 0x150 + SRC, 0xf, 0xf, true));
 }
 
 // f(integral_constant<int, I>) for I = I0 .. N-1, unrolled at compile time.
@@ -2357,102 +2329,288 @@ __device__ __forceinline__ void static_for(F &&f) {
   }
 }
 
+// dlarfg's scalars from alpha and sigma^2 > 0: nrm = sqrt(alpha^2 + sigma^2),
+// beta = -sign(alpha) nrm, tau = (beta - alpha) / beta = 1 + |alpha| / nrm and
+// scal = 1 / (alpha - beta).  The hardware's reciprocal square root and
+// reciprocal start a third-order step each (their relative error cubed, below
+// FP64 rounding), and the norm takes one residual correction; a square root
+// and two divisions by the compiler are a chain of 270 cycles on the
+// factorisation's critical path, this one of about 100.  No intermediate
+// leaves the exponent range for a finite s2, so there is no scaling.
+struct Reflector {
+  double tau, scal, beta;
+};
+__device__ __forceinline__ Reflector make_reflector(double alpha, double sigma2) {
+  Reflector h{0.0, 0.0, alpha};
+  if (!(sigma2 > 0.0)) return h;
+  const double s2 = fma(alpha, alpha, sigma2);
+  const double y0 = __builtin_amdgcn_rsq(s2);
+  const double e = fma(-(s2 * y0), y0, 1.0);
+  const double y = fma(y0 * e, fma(e, 0.375, 0.5), y0);
+  double nrm = s2 * y;
+  nrm = fma(fma(-nrm, nrm, s2), 0.5 * y, nrm);
+  h.beta = alpha >= 0.0 ? -nrm : nrm;
+  h.tau = fma(fabs(alpha), y, 1.0);
+  const double u = alpha - h.beta;
+  const double r0 = __builtin_amdgcn_rcp(u);
+  const double g = fma(-u, r0, 1.0);
+  h.scal = fma(r0, fma(g, g, g), r0);
+  return h;
+}
+
+// LDS of one block's factorisation.  wp holds the waves' partial sums per
+// column, the NW partials of a column side by side (row stride NW + 2: 16
+// lanes write 16 columns without a bank conflict, and a lane reads NW / 4
+// partials as one run).
+template <int NW>
+struct QmShared {
+  double wp[2][16][NW + 2], wq[2][16];
+  double G[16][16];   // G[k][c] = v_c^T v_k, c < k
+  double T[16][17];   // dlarft's T
+  double tau[16];
+};
+
+// Factorises a column tile: columns b0 .. b0 + nbb - 1 of the panel, b0 = 16 b
+// (b < NW, so that the diagonal lies in row tile t = 0 of wave b), reflectors
+// scaled in place below the diagonal, beta on it, T in sh.T (visible to the
+// calling workgroup after its next barrier).
+//
+// Step k broadcasts column k along each 16-lane row and forms, in one pass
+// and one cross-wave sum, x^T a_c for every column c (x = column k below the
+// diagonal); the row-k entries a_kc travel beside them.  Column k's own sum
+// and entry give dlarfg; w_c = a_kc + scal x^T a_c gives dlarf's update of
+// the later columns, and for the earlier ones (their reflectors, not yet
+// scaled) the entry v_c^T v_k = scal_c w_c of V^T V that T is made from, so
+// no pass over V is spent on it.
+//
+// Bound by the dependent chain of a step (one barrier, two sums over the row
+// groups, dlarfg).  After the barrier a lane reads the partials of NW / 4
+// waves and the row groups' sums meet in registers: reading all NW partials
+// of its own and of column k in every lane (18 reads per lane and wave) kept
+// the LDS port busy for 576 cycles of a step's 1400.
+template <int NW, int RT>
+__device__ __forceinline__ void qm_factor(v4d (&a)[RT], int b, int nbb, QmShared<NW> &sh) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lr = lane >> 4, lc = lane & 15, b0 = 16 * b;
+  double my_scal = 0.0, my_beta = 0.0, my_tau = 0.0;  // of column b0 + lc
+  static_for<0, 16>([&](auto KC) __attribute__((always_inline)) {
+    constexpr int kc = decltype(KC)::value, pb = kc & 1;
+    if (kc >= nbb) return;
+    // this lane's first row relative to the block's, opaque so that every
+    // step compares anew instead of keeping 64 lane masks in scalar registers
+    int r0 = 16 * wave + lr - b0;
+    asm volatile("" : "+v"(r0));
+    constexpr bool keep = RT <= 6;  // x held from the sums to the update
+    double x0[4], pp[4], xt[keep ? RT : 1][4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      x0[s] = row_bcast<kc>(a[0][s]);
+      if (r0 + 4 * s <= kc) x0[s] = 0.0;
+      pp[s] = x0[s] * a[0][s];
+    }
+    if (r0 == (kc & 3)) sh.wq[pb][lc] = a[0][kc >> 2];  // the lanes of row k
+#pragma unroll
+    for (int t = 1; t < RT; ++t)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const double x = row_bcast<kc>(a[t][s]);
+        if constexpr (keep) xt[t][s] = x;
+        pp[s] = fma(x, a[t][s], pp[s]);
+      }
+    const double pdot = sum_rows4((pp[0] + pp[1]) + (pp[2] + pp[3]));
+    if (lr == 0) sh.wp[pb][lc][wave] = pdot;
+    __syncthreads();
+    double part = sh.wp[pb][lc][lr * (NW / 4)];
+    const double qc = sh.wq[pb][lc];
+#pragma unroll
+    for (int i = 1; i < NW / 4; ++i) part += sh.wp[pb][lc][lr * (NW / 4) + i];
+    const double pc = sum_rows4(part);
+    const Reflector h = make_reflector(row_bcast<kc>(qc), row_bcast<kc>(pc));
+    const double w = fma(h.scal, pc, qc);
+    if (wave == 0 && lr == 0 && lc < kc) sh.G[kc][lc] = my_scal * w;
+    if (lc == kc) {
+      my_scal = h.scal;
+      my_beta = h.beta;
+      my_tau = h.tau;
+    }
+    // dlarf on the block's columns c > k: a_c -= tau v w_c, v = (1, scal x)
+    const double wt = (lc > kc && lc < nbb) ? -(h.tau * w) : 0.0;
+    const double cs = h.scal * wt;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) a[0][s] = fma(x0[s], cs, a[0][s]);
+    a[0][kc >> 2] += r0 == (kc & 3) ? wt : 0.0;
+#pragma unroll
+    for (int t = 1; t < RT; ++t)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        double x;
+        if constexpr (keep) x = xt[t][s];
+        else x = row_bcast<kc>(a[t][s]);
+        a[t][s] = fma(x, cs, a[t][s]);
+      }
+  });
+  // reflectors scaled in place, beta on the diagonal
+  if (lc < nbb) {
+    const int pr = b0 + lc;
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int row = 16 * (wave + NW * t) + 4 * s + lr;
+        if (t > 0 || row > pr) {
+          if (my_tau != 0.0) a[t][s] *= my_scal;
+        } else if (row == pr) {
+          a[t][s] = my_beta;
+        }
+      }
+  }
+  // T as in dlarft (forward, columnwise), by the wave that holds G: lane
+  // (lr, lc) keeps T[lc][lr + 4u]; column i of T needs columns < i
+  if (wave == 0) {
+    if (lr == 0) sh.tau[lc] = my_tau;
+    wave_lds_order();
+    double tr[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const double ti = i < nbb ? sh.tau[i] : 0.0;
+      double x = 0.0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (4 * u < i && lr + 4 * u < i && i < nbb) x += tr[u] * sh.G[i][lr + 4 * u];
+      x = sum_rows4(x);
+      const double t = lc < i ? -ti * x : (lc == i ? ti : 0.0);
+      if (lr == (i & 3)) tr[i >> 2] = t;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) sh.T[lc][lr + 4 * u] = tr[u];
+  }
+}
+
+// The panel of one item in one visit mode: m true rows, n true columns; entry
+// (row, col) at row rs + (row / n2) ex + col cs of the site's slot.  Only a
+// right-to-left inner site has a gap (ex) between the runs of its rows (l, y')
+// (the physical index major, as in the QR of the transpose).  All offsets
+// stay below 2^23 (bond caps <= 128, P <= 64), so 24-bit products form them:
+// 64-bit offsets took a fifth of a 512 x 32 panel's instructions.
+struct QrPanel {
+  int m, n, rs, cs, n2, ex;
+  __device__ __forceinline__ int row_off(int row, const DivN &d) const {
+    const int o = __mul24(row, rs);
+    return ex ? o + __mul24(d.quot(row), ex) : o;
+  }
+};
+__device__ __forceinline__ QrPanel qr_panel(const QrArgs &q, int it) {
+  const FitDims &dm = q.dims[(size_t)it * q.W + q.c];
+  const int K = q.K, P = q.P, j = q.j;
+  QrPanel p;
+  p.n2 = 1;
+  p.ex = 0;
+  switch (q.mode) {
+    case LR_INNER:
+      p.m = dm.bl[j] * P; p.rs = K; p.n = dm.br[j]; p.cs = 1;
+      break;
+    case RL_INNER:
+      p.m = P * dm.br[j]; p.rs = 1; p.n2 = dm.br[j]; p.ex = K - p.n2; p.n = dm.bl[j];
+      p.cs = P * K;
+      break;
+    case LR_TOP:
+      p.m = dm.p[j]; p.rs = K; p.n = dm.br[j]; p.cs = 1;
+      break;
+    default:  // RL_BOT
+      p.m = dm.p[j]; p.rs = 1; p.n = dm.bl[j]; p.cs = K;
+      break;
+  }
+  p.n = min(p.n, p.m);
+  return p;
+}
+
+// Sum of the waves' 16x16 accumulators into Ws (accumulator slots).
+template <int NW>
+__device__ __forceinline__ void qm_reduce(const v4d &acc, double (*wred)[256], double *Ws) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) wred[wave][r * 64 + lane] = acc[r];
+  __syncthreads();
+  if (tid < 256) {
+    double x = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) x += wred[w][tid];
+    Ws[tid] = x;
+  }
+  __syncthreads();
+}
+
+// -op(T) W as the update's MFMA B operands (register s: row 4s + lr, column
+// lc), every wave for itself: no second pass through LDS.
+__device__ __forceinline__ v4d qm_coeff(const double (*T)[17], bool trans, const double *Ws,
+                                        int lr, int lc) {
+  v4d z = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+    z = mfma16(trans ? T[4 * s + lr][lc] : T[lc][4 * s + lr], Ws[s * 64 + lr * 16 + lc], z);
+  return -z;
+}
+
+// One workgroup per panel of up to 16 NW RT rows and 16 CT columns.  Bound by
+// the chain of column steps.  Against the form that took V^T V by MFMA, formed
+// the block coefficients in a pass of their own through LDS and used 64-bit
+// panel offsets: one 512 x 32 panel 42.6 -> 34.8 us, 672 x 42 (four to
+// sixty-four of them) 120 -> 86 us, 135 x 15 14.7 -> 12.0 us (kernel trace).
 template <int NW, int RT, int CT>
 __global__ __launch_bounds__(NW * 64) void k_qrm(QrArgs q) {
   static_assert(NW % 4 == 0 && NW >= CT && 16 * NW * RT <= kQmRowCap, "panel shape");
   const int it = blockIdx.x;
   if (q.flag && !q.flag[it]) return;
-  const FitDims &dm = q.dims[(size_t)it * q.W + q.c];
-  const int K = q.K, P = q.P, j = q.j;
-  int n1, n2, ncol;
-  size_t s1, s2, sc;
-  switch (q.mode) {
-    case LR_INNER:
-      n1 = dm.bl[j]; s1 = (size_t)P * K; n2 = P; s2 = K; ncol = dm.br[j]; sc = 1;
-      break;
-    case RL_INNER:  // rows (l, yb), l-major, as in the QR of the transpose
-      n1 = P; s1 = K; n2 = dm.br[j]; s2 = 1; ncol = dm.bl[j]; sc = (size_t)P * K;
-      break;
-    case LR_TOP:
-      n1 = dm.p[j]; s1 = K; n2 = 1; s2 = 0; ncol = dm.br[j]; sc = 1;
-      break;
-    default:  // RL_BOT
-      n1 = dm.p[j]; s1 = 1; n2 = 1; s2 = 0; ncol = dm.bl[j]; sc = K;
-      break;
-  }
-  const int m = n1 * n2, n = min(ncol, m);
+  const QrPanel pn = qr_panel(q, it);
+  const int K = q.K, m = pn.m, n = pn.n;
   double *base = q.Y.at(it);
   __shared__ double VT[16 * kQmVs];  // V of the current block, column c at qm_col(c)
   __shared__ double wred[NW][256];
-  __shared__ double Ws[256], Zs[256];
-  __shared__ double Tm[CT][16][16];
-  __shared__ double wp[2][NW][16], wq[2][16];
-  __shared__ double tau_s[16 * CT];
+  __shared__ double Ws[256];
+  __shared__ QmShared<NW> sh[CT];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane >> 4, lc = lane & 15;
   // Row tiles t > 0 start at row 16 * NW >= n, below every diagonal entry.
   auto rowof = [&](int t, int s) { return 16 * (wave + NW * t) + 4 * s + lr; };
-  const DivN dn2(n2);
-  auto gaddr = [&](int row, int col) {
-    const int r1 = dn2.quot(row), r2 = row - r1 * n2;
-    return r1 * s1 + r2 * s2 + col * sc;
-  };
+  const DivN dn2(pn.n2);
 
-  v4d a[RT][CT];
+  // entries outside the panel load past the descriptor's end and read zero
+  const unsigned ybytes = (unsigned)(K * q.P * K) * 8u;
+  const __amdgpu_buffer_rsrc_t yrs = buf_rsrc(base, ybytes);
+  v4d a[CT][RT];
 #pragma unroll
   for (int t = 0; t < RT; ++t)
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct)
+    for (int s = 0; s < 4; ++s) {
+      const int row = rowof(t, s);
+      const unsigned o = (unsigned)(pn.row_off(row, dn2) + __mul24(lc, pn.cs));
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int row = rowof(t, s), col = 16 * ct + lc;
-        a[t][ct][s] = (row < m && col < n) ? base[gaddr(row, col)] : 0.0;
-      }
+      for (int ct = 0; ct < CT; ++ct)
+        a[ct][t][s] = buf_ld(yrs, row < m && 16 * ct + lc < n ? (o + 16 * ct * pn.cs) * 8u : ybytes);
+    }
 
-  // Column tile b's reflectors to LDS: 0 above the diagonal, 1 on it.
-  auto store_v = [&](int b, int nbb) {
+  // entry (row of (t, s), b0 + lc) of V: 0 above the diagonal, 1 on it
+  auto vent = [&](int b, int nbb, int t, int s) __attribute__((always_inline)) {
+    const int row = rowof(t, s), pr = 16 * b + lc;
+    return lc < nbb ? ((t > 0 || row > pr) ? a[b][t][s] : (row == pr ? 1.0 : 0.0)) : 0.0;
+  };
+  auto store_v = [&](int b, int nbb) __attribute__((always_inline)) {
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int row = rowof(t, s), pr = 16 * b + lc;
-        VT[qm_col(lc) + row] = lc < nbb ? ((t > 0 || row > pr) ? a[t][b][s] : (row == pr ? 1.0 : 0.0))
-                               : 0.0;
-      }
+      for (int s = 0; s < 4; ++s) VT[qm_col(lc) + rowof(t, s)] = vent(b, nbb, t, s);
     wave_lds_order();
   };
-
-  // Sum of the per-wave 16x16 accumulators into Ws (accumulator slots).
-  auto reduce_tiles = [&](const v4d &acc) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) wred[wave][r * 64 + lane] = acc[r];
-    __syncthreads();
-    if (tid < 256) {
-      double x = 0.0;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) x += wred[w][tid];
-      Ws[tid] = x;
-    }
-    __syncthreads();
-  };
-
-  // C += V Zs for column tile ct, Zs = -(16x16 coefficients), K = 16 (MFMA)
-  auto update_tile = [&](v4d (&c)[RT]) {
+  // C += V z for a column tile, K = 16 (MFMA)
+  auto update_tile = [&](v4d (&c)[RT], const v4d &z) __attribute__((always_inline)) {
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk)
-        c[t] = mfma16(VT[qm_col(4 * kk + lr) + 16 * (wave + NW * t) + lc],
-                      Zs[(4 * kk + lr) * 16 + lc], c[t]);
+        c[t] = mfma16(VT[qm_col(4 * kk + lr) + 16 * (wave + NW * t) + lc], z[kk], c[t]);
   };
-
   // C -= V op(T) (V^T C) for the column tiles right of block b.
-  auto apply_block = [&](int b, bool trans) {
-    double xo[RT][4];
-#pragma unroll
-    for (int t = 0; t < RT; ++t)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) xo[t][s] = VT[qm_col(lc) + 16 * (wave + NW * t) + 4 * s + lr];
+  auto apply_block = [&](int b, int nbb, bool trans) __attribute__((always_inline)) {
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
       if (ct <= b || 16 * ct >= n) continue;
@@ -2460,237 +2618,82 @@ __global__ __launch_bounds__(NW * 64) void k_qrm(QrArgs q) {
 #pragma unroll
       for (int t = 0; t < RT; ++t)
 #pragma unroll
-        for (int s = 0; s < 4; ++s) acc[s & 1] = mfma16(xo[t][s], a[t][ct][s], acc[s & 1]);
-      reduce_tiles(acc[0] + acc[1]);  // W = V^T C
-      if (tid < 256) {
-        const int p = tid >> 4, jj = tid & 15;
-        double z = 0.0;
-#pragma unroll 4
-        for (int qq = 0; qq < 16; ++qq)
-          z += (trans ? Tm[b][qq][p] : Tm[b][p][qq]) * Ws[cl_index(qq, jj)];
-        Zs[tid] = -z;
-      }
-      __syncthreads();
-      v4d c[RT];
-#pragma unroll
-      for (int t = 0; t < RT; ++t) c[t] = a[t][ct];
-      update_tile(c);
-#pragma unroll
-      for (int t = 0; t < RT; ++t) a[t][ct] = c[t];
+        for (int s = 0; s < 4; ++s)
+          acc[s & 1] = mfma16(vent(b, nbb, t, s), a[ct][t][s], acc[s & 1]);
+      qm_reduce<NW>(acc[0] + acc[1], wred, Ws);  // W = V^T C
+      update_tile(a[ct], qm_coeff(sh[b].T, trans, Ws, lr, lc));
     }
   };
 
   // ---- factorisation (dgeqrf order) ----
-  int pb = 0;
-#pragma unroll
-  for (int b = 0; b < CT; ++b) {
-    const int b0 = 16 * b;
-    if (b0 >= n) break;
-    const int nbb = min(16, n - b0);
-    double my_scal = 0.0, my_beta = 0.0, my_tau = 0.0;  // of column b0 + lc
-    // step kc of the block (KC: an int, or a compile-time constant whose
-    // broadcast takes the source lane as an immediate)
-    auto column = [&](auto KC) {
-      const int kc = KC;
-      if (kc >= nbb) return;
-      const int k = b0 + kc;
-      // x = column k below row k, broadcast along the rows from lane kc
-      double cv[RT * 4], xb[RT * 4];
-#pragma unroll
-      for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int s = 0; s < 4; ++s) cv[t * 4 + s] = a[t][b][s];
-      if constexpr (std::is_integral_v<decltype(KC)>)
-        row_bcast<RT * 4>(xb, cv, kc);  // source lane chosen at run time
-      else
-        newbcast_all<0x150 + decltype(KC)::value, RT * 4>(xb, cv);
-      // x^T a_c over this wave's rows, and the row-k entries a_kc, which the
-      // lanes holding row k store on their own
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int row = rowof(0, s);
-        if (row <= k) xb[s] = 0.0;
-        if (row == k) wq[pb][lc] = a[0][b][s];
-      }
-      double pp[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int s = 0; s < 4; ++s) pp[s] = fma(xb[t * 4 + s], a[t][b][s], pp[s]);
-      const double pdot = sum_rows4((pp[0] + pp[1]) + (pp[2] + pp[3]));
-      if (lr == 0) wp[pb][wave][lc] = pdot;
-      __syncthreads();
-      // x^T a_c over all rows (the waves' partials summed pairwise in a
-      // fixed order), for this lane's column and for column k; every lane
-      // reads the same words per column, so all hold the same bits.  All
-      // reads are issued before the first sum.
-      double vp[NW], vs[NW];
-#pragma unroll
-      for (int ww = 0; ww < NW; ++ww) {
-        vp[ww] = wp[pb][ww][lc];
-        vs[ww] = wp[pb][ww][kc];
-      }
-      const double qc = wq[pb][lc];
-      // dlarfg on column k: sigma^2 = x^T x, alpha = a_kk
-      const double alpha = wq[pb][kc];
-#pragma unroll
-      for (int h = 1; h < NW; h *= 2)
-#pragma unroll
-        for (int ww = 0; ww + h < NW; ww += 2 * h) {
-          vp[ww] += vp[ww + h];
-          vs[ww] += vs[ww + h];
-        }
-      const double pc = vp[0], sigma2 = vs[0];
-      pb ^= 1;
-      double tau = 0.0, scal = 0.0, beta = alpha;
-      if (sigma2 > 0.0) {
-        const double nrm = sqrt(alpha * alpha + sigma2);
-        beta = alpha >= 0.0 ? -nrm : nrm;
-        tau = (beta - alpha) / beta;
-        scal = 1.0 / (alpha - beta);
-      }
-      if (tid == 0) tau_s[k] = tau;
-      if (lc == kc) {
-        my_scal = scal;
-        my_beta = beta;
-        my_tau = tau;
-      }
-      // dlarf on the block's columns c > k: w_c = a_kc + scal x^T a_c,
-      // a_c -= tau v w_c with v = (1, scal x)
-      const double wt = (lc > kc && lc < nbb) ? -(tau * (qc + scal * pc)) : 0.0;
-      const double cs = scal * wt;
-#pragma unroll
-      for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          a[t][b][s] = fma(xb[t * 4 + s], cs, a[t][b][s]);
-          if (t == 0 && rowof(0, s) == k) a[0][b][s] += wt;
-        }
-        };
-    // up to two column tiles the block's steps are unrolled (a lane switch
-    // less per step: 512x32 panels 62.4 -> 54.2 us); at three the unrolled
-    // code outgrows the instruction cache
-    if constexpr (CT <= 2)
-      static_for<0, 16>(column);
-    else
-      for (int kc = 0; kc < nbb; ++kc) column(kc);
-    // reflectors scaled in place, beta on the diagonal
-    if (lc < nbb) {
-      const int pr = b0 + lc;
-#pragma unroll
-      for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const int row = rowof(t, s);
-          if (t > 0 || row > pr) {
-            if (my_tau != 0.0) a[t][b][s] *= my_scal;
-          } else if (row == pr) {
-            a[t][b][s] = my_beta;
-          }
-        }
+  static_for<0, CT>([&](auto B) __attribute__((always_inline)) {
+    constexpr int b = decltype(B)::value;
+    if (16 * b >= n) return;
+    const int nbb = min(16, n - 16 * b);
+    qm_factor<NW, RT>(a[b], b, nbb, sh[b]);
+    if (b + 1 < CT && 16 * (b + 1) < n) {
+      store_v(b, nbb);
+      apply_block(b, nbb, true);
     }
-    store_v(b, nbb);
-
-    // Gram matrix V^T V of the block, then T as in dlarft (forward, columnwise)
-    v4d g[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
-#pragma unroll
-    for (int t = 0; t < RT; ++t)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const double x = VT[qm_col(lc) + 16 * (wave + NW * t) + 4 * s + lr];
-        g[s & 1] = mfma16(x, x, g[s & 1]);
-      }
-    reduce_tiles(g[0] + g[1]);
-    if (wave == 0) {
-      // lane (lr, lc) keeps T[lc][lr + 4u]; column i of T needs columns < i
-      double tr[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const double ti = i < nbb ? tau_s[b0 + i] : 0.0;
-        double x = 0.0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (4 * u < i && lr + 4 * u < i) x += tr[u] * Ws[cl_index(lr + 4 * u, i)];
-        x = sum_rows4(x);
-        const double t = lc < i ? -ti * x : (lc == i ? ti : 0.0);
-        if (lr == (i & 3)) tr[i >> 2] = t;
-        __builtin_amdgcn_sched_barrier(0);
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) Tm[b][lc][lr + 4 * u] = tr[u];
-    }
-    __syncthreads();
-    apply_block(b, true);
-  }
+  });
 
   if (q.want_r) {
     double *Rm = q.rbuf + (size_t)it * K * K;
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int row = rowof(0, s), col = 16 * ct + lc;
-        if (row < K && col < K)
-          Rm[(size_t)row * K + col] =
-              (row < n && col < n && col >= row) ? a[0][ct][s] : 0.0;
-      }
-#pragma unroll
-    for (int t = 1; t < RT; ++t)
+    for (int t = 0; t < RT; ++t)
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
           const int row = rowof(t, s), col = 16 * ct + lc;
-          if (row < K && col < K) Rm[(size_t)row * K + col] = 0.0;
+          if (row < K && col < K)
+            Rm[(size_t)row * K + col] =
+                (t == 0 && row < n && col < n && col >= row) ? a[ct][0][s] : 0.0;
         }
   }
 
   // ---- Q = H_0 ... H_{n-1} [I; 0], backwards over the blocks (dorgqr) ----
-#pragma unroll
-  for (int b = CT - 1; b >= 0; --b) {
-    const int b0 = 16 * b;
-    if (b0 >= n) continue;
+  static_for<0, CT>([&](auto B) __attribute__((always_inline)) {
+    constexpr int b = CT - 1 - decltype(B)::value, b0 = 16 * b;
+    if (b0 >= n) return;
     const int nbb = min(16, n - b0);
+    __syncthreads();  // the previous block's V is no longer read
     store_v(b, nbb);
-    apply_block(b, false);
-    __syncthreads();  // V of every wave visible
+    apply_block(b, nbb, false);
+    __syncthreads();  // V of every wave (and T) visible
     // the block's own columns: E - V (T V_top^T), E the unit columns at rows b0..
-    if (tid < 256) {
-      const int p = tid >> 4, jj = tid & 15;
-      double z = 0.0;
-#pragma unroll 4
-      for (int qq = 0; qq < 16; ++qq) z += Tm[b][p][qq] * VT[qm_col(qq) + b0 + jj];
-      Zs[tid] = -z;
-    }
-    __syncthreads();
+    v4d z = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      z = mfma16(sh[b].T[lc][4 * s + lr], VT[qm_col(4 * s + lr) + b0 + lc], z);
     v4d c[RT];
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
       for (int s = 0; s < 4; ++s)
         c[t][s] = (t == 0 && rowof(0, s) == b0 + lc && lc < nbb) ? 1.0 : 0.0;
-    update_tile(c);
+    update_tile(c, -z);
 #pragma unroll
-    for (int t = 0; t < RT; ++t) a[t][b] = c[t];
-  }
+    for (int t = 0; t < RT; ++t) a[b][t] = c[t];
+  });
 
-  // Recompute the store addresses instead of keeping the load's alive.
-  size_t os1 = s1, os2 = s2, osc = sc;
-  int on2 = n2;
-  asm volatile("" : "+s"(os1), "+s"(os2), "+s"(osc), "+s"(on2));
-  const DivN don2(on2);
+  // The store's offsets and masks are computed anew (opaque sizes) instead of
+  // kept in registers from the load; a masked entry's store is dropped at the
+  // descriptor's end.
+  QrPanel po = pn;
+  asm volatile("" : "+v"(po.m), "+v"(po.n), "+v"(po.rs), "+v"(po.cs), "+v"(po.ex));
 #pragma unroll
   for (int t = 0; t < RT; ++t)
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct)
+    for (int s = 0; s < 4; ++s) {
+      const int row = rowof(t, s);
+      const unsigned o = (unsigned)(po.row_off(row, dn2) + __mul24(lc, po.cs));
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int row = rowof(t, s), col = 16 * ct + lc;
-        const int r1 = don2.quot(row), r2 = row - r1 * on2;
-        if (row < m && col < n) base[r1 * os1 + r2 * os2 + col * osc] = a[t][ct][s];
-      }
+      for (int ct = 0; ct < CT; ++ct)
+        buf_st_t<double>(yrs, row < po.m && 16 * ct + lc < po.n ? (o + 16 * ct * po.cs) * 8u : ybytes,
+                         a[ct][t][s]);
+    }
 }
-
 
 // ---------------------------------------------------------------------------
 // Counter-based uniform numbers: SplitMix64 (Steele, Lea, Flood 2014).

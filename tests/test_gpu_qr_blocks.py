@@ -1,0 +1,55 @@
+"""QR/LQ kernels at the edges of their column blocks and row tiles: one
+message update of a 2 x 2 block with Gaussian messages that fill the bond cap,
+so that its inner panels are (chi D^2) x chi, against the FP64 oracle's column
+absorptions.  The bond caps straddle a column block (16, 17, 33, 49), a row
+tile and the change from the one-workgroup kernel (768 x 48) to the one with a
+workgroup per column tile."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# Messages compared as unit vectors, as in the other message tests: the
+# oracle moves by 1e-14 to 1e-13 when its inputs move by 1e-15.
+TOL = 1e-12
+
+
+def _message(rng, n, P, chi):
+    b = [1] + [min(chi, P ** min(i, n - i)) for i in range(1, n)] + [1]
+    m = [rng.standard_normal((b[i], P, b[i + 1])) for i in range(n)]
+    return [t / np.linalg.norm(t) for t in m], b
+
+
+@pytest.mark.parametrize("D,chi", [
+    (2, 1), (2, 3), (2, 4), (3, 9), (4, 15), (4, 16),   # one column tile
+    (5, 17), (5, 25),                                   # two, D^2 odd
+    (6, 21), (6, 22), (6, 33), (6, 36),                 # 756, 792, 1188, 1296 rows
+    (7, 49),                                            # 2401 x 49: one column in the last tile
+])
+def test_panel_edges(D, chi):
+    import torch
+    from oracle import blockbp as ob
+    from paper_2301_05844_amd import bbp
+    rng = np.random.default_rng(1000 * D + chi)
+    P, H, W = D * D, 2, 2
+    A = 0.3 * rng.standard_normal((H * W, 2, D, D, D, D))
+    A[:, 0, 0, 0, 0, 0] += 1.0
+    sides = [_message(rng, n, P, chi) for n in (W, H, W)]
+    dev = []
+    for m, b in sides:
+        s = np.zeros((len(m), chi, P, chi))
+        for i, t in enumerate(m):
+            s[i, :t.shape[0], :, :t.shape[2]] = t
+        dev.append((torch.from_numpy(s).cuda(), b))
+    out, bonds, scale = bbp.update_message(torch.from_numpy(A).cuda(), *dev, H=H, W=W, D=D,
+                                           chi=chi)
+    grid = [[A[y * W + x] for x in range(W)] for y in range(H)]
+    Y, ls, _, _ = ob.absorb(grid, *[m for m, _ in sides], chi, 2, 0, lambda c: c)
+    ref = ob.extract_message(Y)
+    assert [int(v) for v in bonds] == [1] + [t.shape[2] for t in ref]
+    got = out.cpu().numpy().reshape(H, chi, P, chi)
+    got = [got[i, :bonds[i], :, :bonds[i + 1]] for i in range(H)]
+    g, r = ob.mps_dense(got), ob.mps_dense(ref)
+    assert abs(scale - ls) < TOL
+    assert min(np.abs(g - r).max(), np.abs(g + r).max()) < TOL
