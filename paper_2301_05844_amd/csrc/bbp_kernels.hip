@@ -2280,6 +2280,8 @@ __global__ __launch_bounds__(kQrgThreads) void k_qrg(QrArgs q) {
 // order of sums and updates differs.  Cross-wave sums are taken in a fixed
 // order that every wave repeats, so all waves hold the same bits.
 //
+// Two kernels use it: k_qrm holds a whole panel in one workgroup, k_qrb one
+// column tile per workgroup, a launch per block.
 // ---------------------------------------------------------------------------
 
 constexpr int kQmRowCap = 768;        // rows held by one k_qrm workgroup, at most
@@ -2692,6 +2694,227 @@ __global__ __launch_bounds__(NW * 64) void k_qrm(QrArgs q) {
       for (int ct = 0; ct < CT; ++ct)
         buf_st_t<double>(yrs, row < po.m && 16 * ct + lc < po.n ? (o + 16 * ct * po.cs) * 8u : ybytes,
                          a[ct][t][s]);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The same blocked QR with one column tile per workgroup, for panels that do
+// not fit one workgroup's registers (D = 6: 2304 x 64; D = 4 above bond cap
+// 48), a launch per block of 16 columns.  Launch b (k_qrb_factor): the
+// workgroup of column tile c >= b applies block b - 1 to its tile, and the one
+// of tile b then factorises it; the last launch (k_qrb_q) forms Q, the
+// workgroup of tile c applying blocks c, c - 1, .. 0 to the unit columns, all
+// tiles side by side.  Tiles pass between the launches through a global
+// scratch in the accumulator layout (512 contiguous bytes per register), the
+// reflectors in their own tile as in dgeqrf, T beside them; each workgroup
+// reads a block's V twice (its products need it in both operand layouts, the
+// second turned in LDS by the wave that owns the rows).
+//
+// Bound by the chain: 64 column steps of about 1 us (the VALU work of 2304
+// rows on one CU), then one block application per launch.  One 2304 x 64
+// panel takes 4 launches of 38 us and 43 us for Q, 196 us together; k_qrg, a
+// 16-wave workgroup per panel that streams the trailing panel from L2 once
+// for the dots and once for the update of every column, takes 2739 us, bound
+// by one CU's L2 port.
+// ---------------------------------------------------------------------------
+constexpr int kQrbWaves = 8;
+// scratch doubles of one panel: CT tiles of MT row tiles, then CT T factors
+__host__ __device__ constexpr size_t qrb_words(int K, int P) {
+  const size_t ct = (K + 15) / 16, mt = ((size_t)K * P + 15) / 16;
+  return ct * (mt + 1) * 256;
+}
+
+struct QrbArgs {
+  QrArgs q;
+  int b;   // block of this launch
+  int CT;  // column tiles of the bond cap
+  int MT;  // row tiles of the bond cap
+};
+
+template <int RT>
+struct QrbTile {
+  static constexpr int NW = kQrbWaves;
+  int wave, lane, lr, lc, mt;  // mt: row tiles of the true panel
+  __device__ __forceinline__ QrbTile(int m) {
+    lane = threadIdx.x & 63;
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    lr = lane >> 4;
+    lc = lane & 15;
+    mt = (m + 15) / 16;
+  }
+  __device__ __forceinline__ int rtile(int t) const { return wave + NW * t; }
+  __device__ __forceinline__ bool has(int t) const { return rtile(t) < mt; }
+  // V of block b in row tile t: 0 above the diagonal, 1 on it
+  __device__ __forceinline__ void load_v(const double *scr, int b, int nbb, int MT, int t,
+                                         double (&v)[4]) const {
+    const auto *p = gmem(scr) + ((size_t)b * MT + rtile(t)) * 256 + lane;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      v[s] = p[s * 64];
+      if (t == 0) {  // the only row tiles that reach the diagonal
+        const int d = 16 * (wave - b) + 4 * s + lr - lc;
+        v[s] = d > 0 ? v[s] : (d == 0 ? 1.0 : 0.0);
+      }
+      if (lc >= nbb) v[s] = 0.0;
+    }
+  }
+  // C += V z for the row tiles of this wave; tr: two 16 x 17 tiles of the
+  // wave's own in LDS, used in turn
+  __device__ __forceinline__ void update(v4d (&c)[RT], const double *scr, int b, int nbb, int MT,
+                                         const v4d &z, double (*tr)[16][17]) const {
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      if (!has(t)) continue;
+      double v[4];
+      load_v(scr, b, nbb, MT, t, v);
+      double (*x)[17] = tr[t & 1];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) x[4 * s + lr][lc] = v[s];
+      wave_lds_order();
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) c[t] = mfma16(x[lc][4 * kk + lr], z[kk], c[t]);
+    }
+    wave_lds_order();
+  }
+  // C -= V op(T) (V^T C)
+  __device__ __forceinline__ void apply(v4d (&c)[RT], const double *scr, int b, int nbb, int MT,
+                                        bool trans, const double *Tg, double (*T)[17],
+                                        double (*wred)[256], double *Ws,
+                                        double (*tr)[16][17]) const {
+    if (threadIdx.x < 256) T[threadIdx.x >> 4][threadIdx.x & 15] = gmem(Tg)[threadIdx.x];
+    v4d acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      if (!has(t)) continue;
+      double v[4];
+      load_v(scr, b, nbb, MT, t, v);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) acc[s & 1] = mfma16(v[s], c[t][s], acc[s & 1]);
+    }
+    qm_reduce<NW>(acc[0] + acc[1], wred, Ws);
+    update(c, scr, b, nbb, MT, qm_coeff(T, trans, Ws, lr, lc), tr);
+    __syncthreads();  // T and Ws are refilled by the next block
+  }
+};
+
+template <int RT>
+__global__ __launch_bounds__(kQrbWaves * 64) void k_qrb_factor(QrbArgs g) {
+  constexpr int NW = kQrbWaves;
+  const QrArgs &q = g.q;
+  const int it = blockIdx.x, b = g.b, c = b + blockIdx.y;
+  if (q.flag && !q.flag[it]) return;
+  const QrPanel pn = qr_panel(q, it);
+  const int K = q.K, m = pn.m, n = pn.n;
+  __shared__ QmShared<NW> sh;
+  __shared__ double wred[NW][256], Ws[256];
+  __shared__ double tr[NW][2][16][17];
+  const QrbTile<RT> w(m);
+  double *scr = q.scratch + (size_t)it * q.scratch_stride;
+  double *Tg = scr + (size_t)g.CT * g.MT * 256;
+  double *Rm = q.rbuf + (size_t)it * K * K;
+  if (16 * c >= n) {  // columns past the panel: only R's zeros
+    if (c == b && q.want_r)
+      for (int i = threadIdx.x; i < K * 16; i += NW * 64)
+        if (16 * c + i % 16 < K) gmem(Rm)[(i / 16) * K + 16 * c + i % 16] = 0.0;
+    return;
+  }
+  v4d a[RT];
+  if (b <= 1) {  // from the site's slot
+    const unsigned ybytes = (unsigned)(K * q.P * K) * 8u;
+    const __amdgpu_buffer_rsrc_t yrs = buf_rsrc(q.Y.at(it), ybytes);
+    const DivN dn2(pn.n2);
+    const int col = 16 * c + w.lc;
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int row = 16 * w.rtile(t) + 4 * s + w.lr;
+        const unsigned o = (unsigned)(pn.row_off(row, dn2) + __mul24(col, pn.cs));
+        a[t][s] = buf_ld(yrs, row < m && col < n ? o * 8u : ybytes);
+      }
+  } else {
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        a[t][s] = w.has(t)
+                      ? gmem(scr)[((size_t)c * g.MT + w.rtile(t)) * 256 + s * 64 + w.lane]
+                      : 0.0;
+  }
+  if (b > 0) w.apply(a, scr, b - 1, 16, g.MT, true, Tg + (b - 1) * 256, sh.T, wred, Ws, tr[w.wave]);
+  const int nbb = min(16, n - 16 * b);
+  if (c == b) {
+    qm_factor<NW, RT>(a, b, nbb, sh);
+    if (w.wave == 0) {
+      wave_lds_order();
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        gmem(Tg)[b * 256 + (4 * u + w.lr) * 16 + w.lc] = sh.T[4 * u + w.lr][w.lc];
+    }
+    if (q.want_r) {
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int row = 16 * w.rtile(t) + 4 * s + w.lr, col = 16 * c + w.lc;
+          if (row < K && col < K)
+            gmem(Rm)[row * K + col] = (t == 0 && row < n && col < n && col >= row) ? a[0][s] : 0.0;
+        }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    if (!w.has(t)) continue;
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      gmem(scr)[((size_t)c * g.MT + w.rtile(t)) * 256 + s * 64 + w.lane] = a[t][s];
+  }
+}
+
+template <int RT>
+__global__ __launch_bounds__(kQrbWaves * 64) void k_qrb_q(QrbArgs g) {
+  constexpr int NW = kQrbWaves;
+  const QrArgs &q = g.q;
+  const int it = blockIdx.x, c = g.CT - 1 - (int)blockIdx.y;  // the longest chains first
+  if (q.flag && !q.flag[it]) return;
+  const QrPanel pn = qr_panel(q, it);
+  const int K = q.K, m = pn.m, n = pn.n;
+  if (16 * c >= n) return;
+  __shared__ double T[16][17], wred[NW][256], Ws[256];
+  __shared__ double tr[NW][2][16][17];
+  const QrbTile<RT> w(m);
+  const double *scr = q.scratch + (size_t)it * q.scratch_stride;
+  const double *Tg = scr + (size_t)g.CT * g.MT * 256;
+  const int nbb = min(16, n - 16 * c);
+  v4d a[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      a[t][s] = (t == 0 && 16 * (w.wave - c) + 4 * s + w.lr == w.lc && w.lc < nbb) ? 1.0 : 0.0;
+  // the block's own columns: E - V (T V_top^T)
+  v4d z = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const int k = 4 * s + w.lr;  // V_top[lc][k]
+    double v = gmem(scr)[((size_t)c * g.MT + c) * 256 + cl_index(w.lc, k)];
+    v = k < nbb ? (w.lc > k ? v : (w.lc == k ? 1.0 : 0.0)) : 0.0;
+    z = mfma16(gmem(Tg)[c * 256 + w.lc * 16 + k], v, z);
+  }
+  w.update(a, scr, c, nbb, g.MT, -z, tr[w.wave]);
+  for (int b = c - 1; b >= 0; --b)
+    w.apply(a, scr, b, 16, g.MT, false, Tg + b * 256, T, wred, Ws, tr[w.wave]);
+  const unsigned ybytes = (unsigned)(K * q.P * K) * 8u;
+  const __amdgpu_buffer_rsrc_t yrs = buf_rsrc(q.Y.at(it), ybytes);
+  const DivN dn2(pn.n2);
+  const int col = 16 * c + w.lc;
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int row = 16 * w.rtile(t) + 4 * s + w.lr;
+      const unsigned o = (unsigned)(pn.row_off(row, dn2) + __mul24(col, pn.cs));
+      buf_st_t<double>(yrs, row < m && col < n ? o * 8u : ybytes, a[t][s]);
     }
 }
 
@@ -3219,6 +3442,33 @@ void launch_qrm(const FitBatch &f, hipStream_t st, const QrArgs &q) {
   else launch_qrm_rt<6>(CT, f.items, st, q);
 }
 
+// One column tile per workgroup, a launch per block and one for Q: panels of
+// up to 3072 rows (24 row tiles a wave, all the registers hold) whose scratch
+// is there.  CT + 1 launches instead of one, but each reads the panel once per
+// 16 columns where k_qrg reads it per column.
+template <int RT>
+void launch_qrb_rt(QrbArgs g, int items, hipStream_t st) {
+  for (g.b = 0; g.b < g.CT; ++g.b)
+    hipLaunchKernelGGL((k_qrb_factor<RT>), dim3(items, g.b ? g.CT - g.b : 1),
+                       dim3(kQrbWaves * 64), 0, st, g);
+  hipLaunchKernelGGL((k_qrb_q<RT>), dim3(items, g.CT), dim3(kQrbWaves * 64), 0, st, g);
+}
+
+bool qrb_fits(const FitBatch &f) {
+  return f.K * f.P <= 16 * kQrbWaves * 24 && f.K <= 16 * kQrbWaves &&
+         qrb_words(f.K, f.P) <= t1_stride(f);
+}
+
+void launch_qrb(const FitBatch &f, hipStream_t st, const QrArgs &q) {
+  QrbArgs g{q, 0, (f.K + 15) / 16, (f.K * f.P + 15) / 16};
+  const int rt = (g.MT + kQrbWaves - 1) / kQrbWaves;
+  if (rt <= 4) launch_qrb_rt<4>(g, f.items, st);
+  else if (rt <= 8) launch_qrb_rt<8>(g, f.items, st);
+  else if (rt <= 12) launch_qrb_rt<12>(g, f.items, st);
+  else if (rt <= 18) launch_qrb_rt<18>(g, f.items, st);
+  else launch_qrb_rt<24>(g, f.items, st);
+}
+
 hipError_t launch_inner_visit(const FitBatch &f, int c, int j, bool rl, Ptr X,
                               Ptr F, Ptr G, Ptr Y, hipStream_t st) {
   int TY, TX;
@@ -3369,8 +3619,9 @@ hipError_t launch_qr(const FitBatch &f, int c, int j, int mode, Ptr Y,
   Span sp(KC_QR, st, tc.flops, tc.bytes, f.items * (4.0 * m * n * n - 4.0 * n * n * n / 3.0),
           f.items * 16.0 * m * n);
   // The blocked MFMA kernel for panels up to 768 x 48 (every shape of the
-  // D <= 4 workloads); otherwise the LDS kernel, or the 16-wave global-memory
-  // one (up to 128 columns: every bond cap the context accepts).
+  // D <= 4 workloads); otherwise the LDS kernel, or through the global scratch
+  // a workgroup per column tile up to 3072 rows and the 16-wave kernel beyond
+  // (up to 128 columns: every bond cap the context accepts).
   if (qrm_fits(f)) {
     launch_qrm(f, st, q);
   } else if (panel <= (size_t)kQrLds) {
@@ -3378,6 +3629,10 @@ hipError_t launch_qr(const FitBatch &f, int c, int j, int mode, Ptr Y,
   } else {
     if (!f.t1 || t1_stride(f) < panel)
       return hipErrorInvalidValue;  // global panel scratch missing or too small
+    if (qrb_fits(f)) {
+      launch_qrb(f, st, q);
+      return hipGetLastError();
+    }
     if (f.K > kQrgWaves * kQrgCols) return hipErrorInvalidValue;  // bond caps are <= 128
     hipLaunchKernelGGL(k_qrg, dim3(f.items), dim3(kQrgThreads), 0, st, q);
   }
