@@ -220,6 +220,15 @@ __device__ __forceinline__ void xcd_tile_item(int *tile, int *item) {
   *tile = slot % nx;
 }
 
+// f(integral_constant<int, I>) for I = I0 .. N-1, unrolled at compile time.
+template <int I, int N, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(f);
+  }
+}
+
 // Orders one wave's LDS writes before its later LDS reads (other lanes).
 __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1900,6 +1909,375 @@ void k_visit4p(VisitArgs v) {
 }
 
 // ---------------------------------------------------------------------------
+// The pair-per-wave visit for the other bond dimensions (D = 2, 3, 5, 6;
+// d = 2, bond caps <= 64, FP64).  As above each wave takes one (yf, xb) pair
+// through T1 -> ket -> bra -> T3 -> local update with wave-level LDS ordering,
+// T2 stays in registers, and an xb step has the two barriers of the X/G
+// refill.  The fused leg P = D^2 fills PT = ceil(P / 16) MFMA tiles; a tile's
+// rows and columns past P hold whatever lies behind in LDS and are never
+// stored, only the contracted index needs zeros there (the last k step of a
+// P-long sum masks both operands when 4 does not divide P).  F is held in
+// registers (the A operand of T1, the same for every xb).
+//
+// Bound by MFMA issue on padded tiles (D = 6: 576 MFMAs a pair at K = 64, 64 %
+// of them on real entries; D = 3: 23 at K = 18).  k_visit, which the shapes
+// used before, runs the same contractions phase by phase over one workgroup
+// (six barriers a step, index decodes by division at every element).  A launch
+// there and here: the 24 to 48 messages of a D = 3, chi = 18 sweep 54.6 and
+// 19.4 us, one D = 3, chi = 15 message 24.8 and 9.9 us, one D = 6, chi = 64
+// message 1053 and 105 us (27 TFLOP/s of real entries).
+//
+// Tiles: TX = 4 pairs along xb of one yf (TY = 1) where four X and G tiles
+// fit in LDS (D <= 3; D = 5, 6 up to 32 rows), so that a single message still
+// spreads over K workgroups; otherwise four yf of one xb, with the xb range
+// split over `nsplit` workgroups (see visitp_tiles).
+// ---------------------------------------------------------------------------
+template <int D, int TY, int TX, int NE>
+struct VisitPShape {
+  static constexpr int P = D * D, PT = (P + 15) / 16, PK = (P + 3) / 4, NW = TY * TX,
+                       NT = 64 * NW, XF = 16 * NE;
+  // LDS row strides (doubles): 16 (mod 32) keeps the two k rows a half wave
+  // reads in different banks; D >= 5 with TX = 4 has no room for that
+  static constexpr bool tight = D >= 5 && TX > 1;
+  static constexpr int TS = tight ? P : (P <= 16 ? 16 : 48);
+  static constexpr int GS = tight ? XF : XF + (NE % 2 ? 0 : 16);
+  static constexpr int nT = NW * P * TS, nA = 2 * P * TS, nX = TX * XF * TS, nG = TX * P * GS;
+  static constexpr int nRed = TX > 1 ? NW * PT * NE * 256 : 0;
+  // 64 doubles behind the last array: reads of padded rows and columns
+  static constexpr int body = nT + 2 * nA + nX + nG + 64;
+  static constexpr size_t lds = sizeof(double) * (body > nRed ? body : nRed);
+  static constexpr int LDX = (XF * P * TX + NT - 1) / NT;
+};
+
+struct VisitPArgs {
+  VisitArgs v;
+  int nsplit;        // xb ranges, one per workgroup of a yf tile
+  double *part;      // nsplit > 1: partial Yt, [item][split][K P K]
+  size_t part_stride;
+};
+
+template <int D, int TY, int TX, int NE>
+__global__ __launch_bounds__(64 * TY * TX)
+__attribute__((amdgpu_waves_per_eu(D >= 5 ? 1 : (D == 3 && NE > 2 ? 2 : 3))))
+void k_visitp(VisitPArgs g) {
+  typedef VisitPShape<D, TY, TX, NE> Sh;
+  constexpr int P = Sh::P, PT = Sh::PT, PK = Sh::PK, NT = Sh::NT, XF = Sh::XF, TS = Sh::TS,
+                GS = Sh::GS, LDX = Sh::LDX;
+  extern __shared__ double sm_raw[];
+  const VisitArgs &v = g.v;
+  const int K = v.K;
+  int tile, it;
+  xcd_tile_item(&tile, &it);
+  const int sp = tile % g.nsplit, y0 = (tile / g.nsplit) * TY;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lq = lane >> 4;
+  const int ty = wave / TX, tx = wave % TX, yf = y0 + ty;
+  const bool rl = v.rl != 0;
+  // true extents of this item's operands (see k_visit4p)
+  int nyf = K, nyb = K, nxf = K, nxb = K;
+  if (v.dims) {
+    const SiteExt ex = site_ext(v.dims[(size_t)it * v.W + v.c], v.j, v.N, rl);
+    nyf = ex.yf;
+    nyb = ex.yb;
+    nxf = ex.xf;
+    nxb = ex.xb;
+  }
+  // this workgroup's xb range: nsplit contiguous ranges of whole steps
+  const int steps = (nxb + TX - 1) / TX;
+  const int xlo = steps * sp / g.nsplit * TX, xhi = min(nxb, steps * (sp + 1) / g.nsplit * TX);
+  double *Yout = g.nsplit > 1
+                     ? g.part + (size_t)it * g.part_stride + (size_t)sp * K * P * K
+                     : v.Y.at(it);
+  if (y0 >= nyf) {  // every front bond of the tile is padding: Y rows are zero
+    if (v.do_local) {
+      const int rows = min(TY, K - y0);
+      for (int i = tid; i < rows * P * K; i += NT) {
+        const int yb = i % K, l = (i / K) % P, y = y0 + i / (K * P);
+        gmem(Yout)[rl ? ((size_t)yb * P + l) * K + y : ((size_t)y * P + l) * K + yb] = 0.0;
+      }
+    }
+    return;
+  }
+  double *Tp = sm_raw + wave * P * TS;  // this wave's T1, then T3
+  double *Ak = sm_raw + Sh::nT;
+  double *Ab = Ak + Sh::nA;
+  double *Xs = Ab + Sh::nA;
+  double *Gs = Xs + Sh::nX;
+  const unsigned xgbytes = (unsigned)K * P * K * 8u;
+  const __amdgpu_buffer_rsrc_t xrs = buf_rsrc(v.X.at(it), xgbytes);
+  const __amdgpu_buffer_rsrc_t frs = buf_rsrc(v.F.at(it), xgbytes);
+  const __amdgpu_buffer_rsrc_t grs = buf_rsrc(v.do_local ? v.G.at(it) : v.X.at(it), xgbytes);
+  double *T3g = v.t3 + (size_t)it * v.t3_stride;
+  const __amdgpu_buffer_rsrc_t t3rs = buf_rsrc(T3g, (unsigned)K * P * K * P * 8u);
+
+  // site tensors of the front view (RL swaps u and d) as [s][wf, a][l, wb]
+  {
+    const auto *ak = gmem(v.aket + (size_t)it * v.aket_stride);
+    const auto *ab = gmem(v.abra + (size_t)it * v.abra_stride);
+    for (int i = tid; i < 2 * P * P; i += NT) {
+      const int n = i % P, k = (i / P) % P, s = i / (P * P);
+      const int wb = n % D, l = n / D, a = k % D, wf = k / D;
+      const int src = (((s * D + (rl ? wb : wf)) * D + l) * D + (rl ? wf : wb)) * D + a;
+      Ak[(s * P + k) * TS + n] = ak[src];
+      Ab[(s * P + k) * TS + n] = ab[src];
+    }
+  }
+  // F rows of this wave's yf: A operand of T1 (row wf, k = xf), zero outside
+  double fr[PT][4 * NE];
+#pragma unroll
+  for (int mt = 0; mt < PT; ++mt)
+#pragma unroll
+    for (int ks = 0; ks < 4 * NE; ++ks) {
+      const int wf = 16 * mt + lr, xf = 4 * ks + lq;
+      const bool ok = wf < P && xf < nxf && yf < nyf;
+      fr[mt][ks] = buf_ld(frs, ok ? (unsigned)((yf * P + wf) * K + xf) * 8u : xgbytes);
+    }
+  v4d accE[PT][NE];
+#pragma unroll
+  for (int mt = 0; mt < PT; ++mt)
+#pragma unroll
+    for (int q = 0; q < NE; ++q) accE[mt][q] = v4d{0.0, 0.0, 0.0, 0.0};
+
+  // X [xf][a] and G [wb][yb] of the next step, fetched into registers while
+  // the current one computes (up to 10 elements a thread; where TX = 4 tiles
+  // of D >= 5 take more, they are loaded at the refill: a step there computes
+  // for 13 us); elements outside load past the descriptor's end (zero).
+  // Element u of a thread is i = tid + NT u of [tx][a][xf] (RL) or
+  // [xf][a][tx] (LR), and of [yb][wb][tx].
+  constexpr bool pre = LDX <= 10;
+  double xr[LDX], gr[LDX];
+  auto xdec = [&](int u, int &txx, int &a, int &xf) __attribute__((always_inline)) {
+    const int i = tid + u * NT;
+    if (rl) {
+      xf = i % XF;
+      a = (i / XF) % P;
+      txx = i / (XF * P);
+    } else {
+      txx = i % TX;
+      a = (i / TX) % P;
+      xf = i / (TX * P);
+    }
+  };
+  auto gdec = [&](int u, int &txx, int &wb, int &yb) __attribute__((always_inline)) {
+    const int i = tid + u * NT;
+    txx = i % TX;
+    wb = (i / TX) % P;
+    yb = i / (TX * P);
+  };
+  auto fetch = [&](int x0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < LDX; ++u) {
+      int txx, a, xf;
+      xdec(u, txx, a, xf);
+      const int xb = x0 + txx;
+      const bool ok = tid + u * NT < XF * P * TX && xf < nxf && xb < xhi;
+      const unsigned off = rl ? (xb * P + a) * K + xf : (xf * P + a) * K + xb;
+      xr[u] = buf_ld(xrs, ok ? off * 8u : xgbytes);
+    }
+    if (v.do_local) {
+#pragma unroll
+      for (int u = 0; u < LDX; ++u) {
+        int txx, wb, yb;
+        gdec(u, txx, wb, yb);
+        const int xb = x0 + txx;
+        const bool ok = tid + u * NT < XF * P * TX && yb < nyb && xb < xhi;
+        gr[u] = buf_ld(grs, ok ? (unsigned)((yb * P + wb) * K + xb) * 8u : xgbytes);
+      }
+    }
+  };
+  auto refill = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < LDX; ++u) {
+      int txx, a, xf;
+      xdec(u, txx, a, xf);
+      if (tid + u * NT < XF * P * TX) Xs[(txx * XF + xf) * TS + a] = xr[u];
+    }
+    if (v.do_local) {
+#pragma unroll
+      for (int u = 0; u < LDX; ++u) {
+        int txx, wb, yb;
+        gdec(u, txx, wb, yb);
+        if (tid + u * NT < XF * P * TX) Gs[(txx * P + wb) * GS + yb] = gr[u];
+      }
+    }
+  };
+  if (pre && xlo < xhi) fetch(xlo);
+
+  for (int x0 = xlo; x0 < xhi; x0 += TX) {
+    if (!pre) fetch(x0);
+    __syncthreads();  // the previous step's readers of Xs and Gs are done
+    refill();
+    __syncthreads();
+    if (pre && x0 + TX < xhi) fetch(x0 + TX);
+    const int xb = x0 + tx;
+    if (xb >= xhi || yf >= nyf) continue;  // a wave without a pair
+    // (a) T1: rows wf, cols a, k = xf; stored [wfk, akx][wfb, abx]
+    {
+      v4d acc[PT][PT];
+#pragma unroll
+      for (int mt = 0; mt < PT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < PT; ++nt) acc[mt][nt] = v4d{0.0, 0.0, 0.0, 0.0};
+      const double *px = Xs + (tx * XF + lq) * TS + lr;
+      static_for<0, 4 * NE>([&](auto KS) __attribute__((always_inline)) {
+        constexpr int ks = decltype(KS)::value;
+        if (4 * ks >= nxf) return;
+#pragma unroll
+        for (int nt = 0; nt < PT; ++nt) {
+          const double b = px[4 * ks * TS + 16 * nt];
+#pragma unroll
+          for (int mt = 0; mt < PT; ++mt) acc[mt][nt] = mfma16(fr[mt][ks], b, acc[mt][nt]);
+        }
+        // large tiles: operand reads stay near their MFMAs, not in registers
+        if (PT > 1 && ks % 2) __builtin_amdgcn_sched_barrier(0);
+      });
+#pragma unroll
+      for (int mt = 0; mt < PT; ++mt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int wf = 16 * mt + 4 * r + lq;
+          if (16 * mt + 4 * r >= P) continue;
+#pragma unroll
+          for (int nt = 0; nt < PT; ++nt) {
+            const int a = 16 * nt + lr;
+            if (wf < P && a < P)
+              Tp[((wf / D) * D + a / D) * TS + (wf % D) * D + a % D] = acc[mt][nt][r];
+          }
+        }
+    }
+    wave_lds_order();
+    // (b), (c) per column tile (lk, wbk) of the ket's output: its accumulator
+    // register i of tile mt is the bra's A operand for k = 16 mt + 4 i + lq
+    v4d t3[PT][PT];
+#pragma unroll
+    for (int nt = 0; nt < PT; ++nt) {
+#pragma unroll
+      for (int n2 = 0; n2 < PT; ++n2) t3[nt][n2] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        v4d t2[PT];
+#pragma unroll
+        for (int mt = 0; mt < PT; ++mt) t2[mt] = v4d{0.0, 0.0, 0.0, 0.0};
+        const double *pa = Tp + lq * TS + lr, *pb = Ak + (s * P + lq) * TS + 16 * nt + lr;
+#pragma unroll
+        for (int ks = 0; ks < PK; ++ks) {
+          const bool in = 4 * ks + 3 < P || 4 * ks + lq < P;
+          const double b = in ? pb[4 * ks * TS] : 0.0;
+#pragma unroll
+          for (int mt = 0; mt < PT; ++mt)
+            t2[mt] = mfma16(in ? pa[4 * ks * TS + 16 * mt] : 0.0, b, t2[mt]);
+          if (PT > 1 && ks % 2) __builtin_amdgcn_sched_barrier(0);
+        }
+        const double *pc = Ab + (s * P + lq) * TS + lr;
+#pragma unroll
+        for (int mt = 0; mt < PT; ++mt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int k0 = 16 * mt + 4 * i;
+            if (k0 >= P) continue;
+            const bool in = k0 + 3 < P || k0 + lq < P;
+            const double a = in ? t2[mt][i] : 0.0;
+#pragma unroll
+            for (int n2 = 0; n2 < PT; ++n2)
+              t3[nt][n2] = mfma16(a, in ? pc[k0 * TS + 16 * n2] : 0.0, t3[nt][n2]);
+            if (PT > 1 && i % 2) __builtin_amdgcn_sched_barrier(0);
+          }
+      }
+    }
+    wave_lds_order();  // every lane's T1 reads precede the T3 writes below
+#pragma unroll
+    for (int nt = 0; nt < PT; ++nt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = 16 * nt + 4 * r + lq;  // (lk, wbk)
+        if (16 * nt + 4 * r >= P) continue;
+#pragma unroll
+        for (int n2 = 0; n2 < PT; ++n2) {
+          const int n = 16 * n2 + lr;  // (lb, wbb)
+          if (m < P && n < P)
+            Tp[((m % D) * D + n % D) * TS + (m / D) * D + n / D] = t3[nt][n2][r];
+        }
+      }
+    wave_lds_order();
+    // T3 of the pair to HBM as T3[yf][l][xb][wb]
+#pragma unroll
+    for (int u = 0; u < (P * P + 63) / 64; ++u) {
+      const int i = lane + 64 * u, wb = i % P, l = i / P;
+      if (i < P * P)
+        buf_st_t<double>(t3rs, (unsigned)(((yf * P + l) * K + xb) * P + wb) * 8u, Tp[wb * TS + l]);
+    }
+    // (e) this pair's contribution to Yt[l][yb]: k = wb
+    if (v.do_local) {
+      const double *pa = Tp + lq * TS + lr, *pb = Gs + (tx * P + lq) * GS + lr;
+#pragma unroll
+      for (int ks = 0; ks < PK; ++ks) {
+        const bool in = 4 * ks + 3 < P || 4 * ks + lq < P;
+        double a[PT];
+#pragma unroll
+        for (int mt = 0; mt < PT; ++mt) a[mt] = in ? pa[4 * ks * TS + 16 * mt] : 0.0;
+#pragma unroll
+        for (int q = 0; q < NE; ++q) {
+          if (16 * q >= nyb) break;
+          const double b = in ? pb[4 * ks * GS + 16 * q] : 0.0;
+#pragma unroll
+          for (int mt = 0; mt < PT; ++mt) accE[mt][q] = mfma16(a[mt], b, accE[mt][q]);
+        }
+        if (PT > 1) __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  if (!v.do_local) return;
+  if constexpr (TX > 1) {  // sum the TX partials of each yf in a fixed order
+    __syncthreads();
+#pragma unroll
+    for (int mt = 0; mt < PT; ++mt)
+#pragma unroll
+      for (int q = 0; q < NE; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          sm_raw[(((wave * PT + mt) * NE + q) * 4 + r) * 64 + lane] = accE[mt][q][r];
+    __syncthreads();
+    if (tx != 0) return;
+#pragma unroll
+    for (int mt = 0; mt < PT; ++mt)
+#pragma unroll
+      for (int q = 0; q < NE; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int o = 1; o < TX; ++o)
+            accE[mt][q][r] += sm_raw[((((wave + o) * PT + mt) * NE + q) * 4 + r) * 64 + lane];
+  }
+  if (yf >= K) return;
+#pragma unroll
+  for (int mt = 0; mt < PT; ++mt)
+#pragma unroll
+    for (int q = 0; q < NE; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int l = 16 * mt + 4 * r + lq, yb = 16 * q + lr;
+        if (l < P && yb < K)
+          gmem(Yout)[rl ? ((size_t)yb * P + l) * K + yf : ((size_t)yf * P + l) * K + yb] =
+              accE[mt][q][r];
+      }
+}
+
+// Y = the sum of the nsplit partial Yt of each item, in order.
+__global__ __launch_bounds__(kThreads) void k_sum_parts(Ptr Y, const double *part,
+                                                        size_t part_stride, int nsplit, size_t n) {
+  const int it = blockIdx.y;
+  const auto *p = gmem(part) + (size_t)it * part_stride;
+  auto *y = gmem(Y.at(it));
+  for (size_t i = blockIdx.x * (size_t)kThreads + threadIdx.x; i < n;
+       i += (size_t)gridDim.x * kThreads) {
+    double t = p[i];
+    for (int k = 1; k < nsplit; ++k) t += p[(size_t)k * n + i];
+    y[i] = t;
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Householder QR (LAPACK conventions: dlarfg reflectors, dorg2r formation).
 // One workgroup per item; the true panel (rows r = r1*n2 + r2, columns c at
 // base[r1*s1 + r2*s2 + c*sc]) is copied column-major into LDS, factorised,
@@ -2284,14 +2662,13 @@ __global__ __launch_bounds__(kQrgThreads) void k_qrg(QrArgs q) {
 // column tile per workgroup, a launch per block.
 // ---------------------------------------------------------------------------
 
-constexpr int kQmRowCap = 768;        // rows held by one k_qrm workgroup, at most
-// V column c of the block starts at c * kQmVs + (c & 14) doubles: with the
-// column stride 16 (mod 32) and that shift, both the per-lane column walk
-// (lane (lr, lc) reads column lc, rows 4s + lr) and the MFMA operand read
-// (column 4kk + lr, row lc) touch 32 distinct banks per half-wave, and the
-// per-lane part of every address stays a base plus compile-time offsets.
-constexpr int kQmVs = kQmRowCap + 16;
-__device__ __forceinline__ int qm_col(int c) { return c * kQmVs + (c & 14); }
+// V column c of the block starts at c * VS + (c & 14) doubles: with the column
+// stride VS = 16 (mod 32) and that shift, both the per-lane column walk (lane
+// (lr, lc) reads column lc, rows 4s + lr) and the MFMA operand read (column
+// 4kk + lr, row lc) touch 32 distinct banks per half-wave, and the per-lane
+// part of every address stays a base plus compile-time offsets.
+template <int VS>
+__device__ __forceinline__ int qm_col(int c) { return c * VS + (c & 14); }
 
 __device__ __forceinline__ double join_f64(int lo, int hi) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
@@ -2322,23 +2699,16 @@ __device__ __forceinline__ double row_bcast(double x) {
       __builtin_amdgcn_mov_dpp(__double_as_longlong(x), 0x150 + SRC, 0xf, 0xf, true));
 }
 
-// f(integral_constant<int, I>) for I = I0 .. N-1, unrolled at compile time.
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for(F &&f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<I + 1, N>(f);
-  }
-}
-
 // dlarfg's scalars from alpha and sigma^2 > 0: nrm = sqrt(alpha^2 + sigma^2),
-// beta = -sign(alpha) nrm, tau = (beta - alpha) / beta = 1 + |alpha| / nrm and
-// scal = 1 / (alpha - beta).  The hardware's reciprocal square root and
-// reciprocal start a third-order step each (their relative error cubed, below
-// FP64 rounding), and the norm takes one residual correction; a square root
-// and two divisions by the compiler are a chain of 270 cycles on the
-// factorisation's critical path, this one of about 100.  No intermediate
-// leaves the exponent range for a finite s2, so there is no scaling.
+// beta = -sign(alpha) nrm, tau = (beta - alpha) / beta, scal = 1 / (alpha -
+// beta).  The hardware's reciprocal square root and reciprocal start a
+// third-order step each (their relative error cubed, below FP64 rounding), and
+// one residual correction rounds each result as a division or square root
+// would: panels whose columns depend on each other rely on exact values (tau
+// = 2 where sigma vanishes beside alpha).  The compiler's square root and two
+// divisions are a chain of 270 cycles on the factorisation's critical path,
+// this one of about 130.  No intermediate leaves the exponent range for a
+// finite s2, so there is no scaling.
 struct Reflector {
   double tau, scal, beta;
 };
@@ -2352,11 +2722,15 @@ __device__ __forceinline__ Reflector make_reflector(double alpha, double sigma2)
   double nrm = s2 * y;
   nrm = fma(fma(-nrm, nrm, s2), 0.5 * y, nrm);
   h.beta = alpha >= 0.0 ? -nrm : nrm;
-  h.tau = fma(fabs(alpha), y, 1.0);
   const double u = alpha - h.beta;
   const double r0 = __builtin_amdgcn_rcp(u);
   const double g = fma(-u, r0, 1.0);
-  h.scal = fma(r0, fma(g, g, g), r0);
+  const double r1 = fma(r0, fma(g, g, g), r0);
+  h.scal = fma(r1, fma(-u, r1, 1.0), r1);
+  // tau = |u| / nrm, with 1 / nrm from y
+  const double yn = fma(y, fma(-nrm, y, 1.0), y), ua = fabs(u);
+  const double t = ua * yn;
+  h.tau = fma(fma(-t, nrm, ua), yn, t);
   return h;
 }
 
@@ -2391,8 +2765,9 @@ struct QmShared {
 // of its own and of column k in every lane (18 reads per lane and wave) kept
 // the LDS port busy for 576 cycles of a step's 1400.
 template <int NW, int RT>
-__device__ __forceinline__ void qm_factor(v4d (&a)[RT], int b, int nbb, QmShared<NW> &sh) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+__device__ __forceinline__ void qm_factor(v4d (&a)[RT], int b, int nbb, QmShared<NW> &sh,
+                                          int tid = threadIdx.x) {
+  const int lane = tid & 63, wave = tid >> 6;
   const int lr = lane >> 4, lc = lane & 15, b0 = 16 * b;
   double my_scal = 0.0, my_beta = 0.0, my_tau = 0.0;  // of column b0 + lc
   static_for<0, 16>([&](auto KC) __attribute__((always_inline)) {
@@ -2528,8 +2903,9 @@ __device__ __forceinline__ QrPanel qr_panel(const QrArgs &q, int it) {
 
 // Sum of the waves' 16x16 accumulators into Ws (accumulator slots).
 template <int NW>
-__device__ __forceinline__ void qm_reduce(const v4d &acc, double (*wred)[256], double *Ws) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+__device__ __forceinline__ void qm_reduce(const v4d &acc, double (*wred)[256], double *Ws,
+                                          int tid = threadIdx.x) {
+  const int lane = tid & 63, wave = tid >> 6;
 #pragma unroll
   for (int r = 0; r < 4; ++r) wred[wave][r * 64 + lane] = acc[r];
   __syncthreads();
@@ -2553,6 +2929,108 @@ __device__ __forceinline__ v4d qm_coeff(const double (*T)[17], bool trans, const
   return -z;
 }
 
+// LDS of a panel's factorisation in one workgroup.
+template <int NW, int RT, int CT>
+struct QmBuf {
+  static constexpr int VS = 16 * NW * RT + 16;
+  double VT[16 * VS];  // V of the current block, column c at qm_col(c)
+  double wred[NW][256];
+  double Ws[256];
+  QmShared<NW> sh[CT];
+};
+
+// QR of a panel held in registers by one workgroup of NW waves: a[ct][t]
+// register s of lane (lr, lc) is row 16 (wave + NW t) + 4 s + lr, column 16 ct
+// + lc, zero outside the n columns and the true rows.  on_r() is called with R
+// on and above a's diagonal; then a becomes Q.
+template <int NW, int RT, int CT, class F>
+__device__ __forceinline__ void qm_panel(v4d (&a)[CT][RT], int n, QmBuf<NW, RT, CT> &sm,
+                                         F &&on_r, int tid = threadIdx.x) {
+  static_assert(NW % 4 == 0 && NW >= CT, "panel shape");
+  constexpr int VS = QmBuf<NW, RT, CT>::VS;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int lr = lane >> 4, lc = lane & 15;
+  double *VT = sm.VT, *Ws = sm.Ws;
+  // Row tiles t > 0 start at row 16 * NW >= n, below every diagonal entry.
+  auto rowof = [&](int t, int s) __attribute__((always_inline)) {
+    return 16 * (wave + NW * t) + 4 * s + lr;
+  };
+  // entry (row of (t, s), b0 + lc) of V: 0 above the diagonal, 1 on it
+  auto vent = [&](int b, int nbb, int t, int s) __attribute__((always_inline)) {
+    const int row = rowof(t, s), pr = 16 * b + lc;
+    return lc < nbb ? ((t > 0 || row > pr) ? a[b][t][s] : (row == pr ? 1.0 : 0.0)) : 0.0;
+  };
+  auto store_v = [&](int b, int nbb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) VT[qm_col<VS>(lc) + rowof(t, s)] = vent(b, nbb, t, s);
+    wave_lds_order();
+  };
+  // C += V z for a column tile, K = 16 (MFMA)
+  auto update_tile = [&](v4d (&c)[RT], const v4d &z) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+        c[t] = mfma16(VT[qm_col<VS>(4 * kk + lr) + 16 * (wave + NW * t) + lc], z[kk], c[t]);
+  };
+  // C -= V op(T) (V^T C) for the column tiles right of block b.
+  auto apply_block = [&](int b, int nbb, bool trans) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      if (ct <= b || 16 * ct >= n) continue;
+      v4d acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+          acc[s & 1] = mfma16(vent(b, nbb, t, s), a[ct][t][s], acc[s & 1]);
+      qm_reduce<NW>(acc[0] + acc[1], sm.wred, Ws, tid);  // W = V^T C
+      update_tile(a[ct], qm_coeff(sm.sh[b].T, trans, Ws, lr, lc));
+    }
+  };
+
+  // ---- factorisation (dgeqrf order) ----
+  static_for<0, CT>([&](auto B) __attribute__((always_inline)) {
+    constexpr int b = decltype(B)::value;
+    if (16 * b >= n) return;
+    const int nbb = min(16, n - 16 * b);
+    qm_factor<NW, RT>(a[b], b, nbb, sm.sh[b], tid);
+    if (b + 1 < CT && 16 * (b + 1) < n) {
+      store_v(b, nbb);
+      apply_block(b, nbb, true);
+    }
+  });
+
+  on_r();
+
+  // ---- Q = H_0 ... H_{n-1} [I; 0], backwards over the blocks (dorgqr) ----
+  static_for<0, CT>([&](auto B) __attribute__((always_inline)) {
+    constexpr int b = CT - 1 - decltype(B)::value, b0 = 16 * b;
+    if (b0 >= n) return;
+    const int nbb = min(16, n - b0);
+    __syncthreads();  // the previous block's V is no longer read
+    store_v(b, nbb);
+    apply_block(b, nbb, false);
+    __syncthreads();  // V of every wave (and T) visible
+    // the block's own columns: E - V (T V_top^T), E the unit columns at rows b0..
+    v4d z = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      z = mfma16(sm.sh[b].T[lc][4 * s + lr], VT[qm_col<VS>(4 * s + lr) + b0 + lc], z);
+    v4d c[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        c[t][s] = (t == 0 && rowof(0, s) == b0 + lc && lc < nbb) ? 1.0 : 0.0;
+    update_tile(c, -z);
+#pragma unroll
+    for (int t = 0; t < RT; ++t) a[b][t] = c[t];
+  });
+}
+
 // One workgroup per panel of up to 16 NW RT rows and 16 CT columns.  Bound by
 // the chain of column steps.  Against the form that took V^T V by MFMA, formed
 // the block coefficients in a pass of their own through LDS and used 64-bit
@@ -2560,19 +3038,14 @@ __device__ __forceinline__ v4d qm_coeff(const double (*T)[17], bool trans, const
 // sixty-four of them) 120 -> 86 us, 135 x 15 14.7 -> 12.0 us (kernel trace).
 template <int NW, int RT, int CT>
 __global__ __launch_bounds__(NW * 64) void k_qrm(QrArgs q) {
-  static_assert(NW % 4 == 0 && NW >= CT && 16 * NW * RT <= kQmRowCap, "panel shape");
   const int it = blockIdx.x;
   if (q.flag && !q.flag[it]) return;
   const QrPanel pn = qr_panel(q, it);
   const int K = q.K, m = pn.m, n = pn.n;
   double *base = q.Y.at(it);
-  __shared__ double VT[16 * kQmVs];  // V of the current block, column c at qm_col(c)
-  __shared__ double wred[NW][256];
-  __shared__ double Ws[256];
-  __shared__ QmShared<NW> sh[CT];
+  __shared__ QmBuf<NW, RT, CT> sm;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane >> 4, lc = lane & 15;
-  // Row tiles t > 0 start at row 16 * NW >= n, below every diagonal entry.
   auto rowof = [&](int t, int s) { return 16 * (wave + NW * t) + 4 * s + lr; };
   const DivN dn2(pn.n2);
 
@@ -2591,55 +3064,8 @@ __global__ __launch_bounds__(NW * 64) void k_qrm(QrArgs q) {
         a[ct][t][s] = buf_ld(yrs, row < m && 16 * ct + lc < n ? (o + 16 * ct * pn.cs) * 8u : ybytes);
     }
 
-  // entry (row of (t, s), b0 + lc) of V: 0 above the diagonal, 1 on it
-  auto vent = [&](int b, int nbb, int t, int s) __attribute__((always_inline)) {
-    const int row = rowof(t, s), pr = 16 * b + lc;
-    return lc < nbb ? ((t > 0 || row > pr) ? a[b][t][s] : (row == pr ? 1.0 : 0.0)) : 0.0;
-  };
-  auto store_v = [&](int b, int nbb) __attribute__((always_inline)) {
-#pragma unroll
-    for (int t = 0; t < RT; ++t)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) VT[qm_col(lc) + rowof(t, s)] = vent(b, nbb, t, s);
-    wave_lds_order();
-  };
-  // C += V z for a column tile, K = 16 (MFMA)
-  auto update_tile = [&](v4d (&c)[RT], const v4d &z) __attribute__((always_inline)) {
-#pragma unroll
-    for (int t = 0; t < RT; ++t)
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-        c[t] = mfma16(VT[qm_col(4 * kk + lr) + 16 * (wave + NW * t) + lc], z[kk], c[t]);
-  };
-  // C -= V op(T) (V^T C) for the column tiles right of block b.
-  auto apply_block = [&](int b, int nbb, bool trans) __attribute__((always_inline)) {
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-      if (ct <= b || 16 * ct >= n) continue;
-      v4d acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
-#pragma unroll
-      for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-          acc[s & 1] = mfma16(vent(b, nbb, t, s), a[ct][t][s], acc[s & 1]);
-      qm_reduce<NW>(acc[0] + acc[1], wred, Ws);  // W = V^T C
-      update_tile(a[ct], qm_coeff(sh[b].T, trans, Ws, lr, lc));
-    }
-  };
-
-  // ---- factorisation (dgeqrf order) ----
-  static_for<0, CT>([&](auto B) __attribute__((always_inline)) {
-    constexpr int b = decltype(B)::value;
-    if (16 * b >= n) return;
-    const int nbb = min(16, n - 16 * b);
-    qm_factor<NW, RT>(a[b], b, nbb, sh[b]);
-    if (b + 1 < CT && 16 * (b + 1) < n) {
-      store_v(b, nbb);
-      apply_block(b, nbb, true);
-    }
-  });
-
-  if (q.want_r) {
+  qm_panel<NW, RT, CT>(a, n, sm, [&]() __attribute__((always_inline)) {
+    if (!q.want_r) return;
     double *Rm = q.rbuf + (size_t)it * K * K;
 #pragma unroll
     for (int t = 0; t < RT; ++t)
@@ -2652,31 +3078,6 @@ __global__ __launch_bounds__(NW * 64) void k_qrm(QrArgs q) {
             Rm[(size_t)row * K + col] =
                 (t == 0 && row < n && col < n && col >= row) ? a[ct][0][s] : 0.0;
         }
-  }
-
-  // ---- Q = H_0 ... H_{n-1} [I; 0], backwards over the blocks (dorgqr) ----
-  static_for<0, CT>([&](auto B) __attribute__((always_inline)) {
-    constexpr int b = CT - 1 - decltype(B)::value, b0 = 16 * b;
-    if (b0 >= n) return;
-    const int nbb = min(16, n - b0);
-    __syncthreads();  // the previous block's V is no longer read
-    store_v(b, nbb);
-    apply_block(b, nbb, false);
-    __syncthreads();  // V of every wave (and T) visible
-    // the block's own columns: E - V (T V_top^T), E the unit columns at rows b0..
-    v4d z = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-      z = mfma16(sh[b].T[lc][4 * s + lr], VT[qm_col(4 * s + lr) + b0 + lc], z);
-    v4d c[RT];
-#pragma unroll
-    for (int t = 0; t < RT; ++t)
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-        c[t][s] = (t == 0 && rowof(0, s) == b0 + lc && lc < nbb) ? 1.0 : 0.0;
-    update_tile(c, -z);
-#pragma unroll
-    for (int t = 0; t < RT; ++t) a[b][t] = c[t];
   });
 
   // The store's offsets and masks are computed anew (opaque sizes) instead of
@@ -3322,6 +3723,65 @@ static Count count_qr(const FitBatch &f, int c, int j, int mode) {
   return t;
 }
 
+// The pair-per-wave visit of the other bond dimensions: its kernel, tile and
+// LDS for this batch, or false (D = 4, other d, bond caps above 64 and the
+// FP32 and BF16 contractions have kernels of their own).  The tile depends on
+// the shape alone; only the xb split of D >= 5 above 32 rows looks at the
+// batch, through the items the tiling is chosen for.
+using VisitPKernel = void (*)(VisitPArgs);
+struct VisitPChoice {
+  VisitPKernel k = nullptr;
+  int TY = 1, threads = 0, nsplit = 1;
+  size_t lds = 0;
+};
+template <int D, int TY, int TX, int NE>
+static VisitPChoice visitp_choice() {
+  typedef VisitPShape<D, TY, TX, NE> Sh;
+  static_assert(Sh::lds <= 160 * 1024, "LDS of one workgroup");
+  return VisitPChoice{k_visitp<D, TY, TX, NE>, TY, Sh::NT, 1, Sh::lds};
+}
+template <int D>
+static VisitPChoice visitp_small(int ne) {
+  switch (ne) {
+    case 1: return visitp_choice<D, 1, 4, 1>();
+    case 2: return visitp_choice<D, 1, 4, 2>();
+    case 3: return visitp_choice<D, 1, 4, 3>();
+    default: return visitp_choice<D, 1, 4, 4>();
+  }
+}
+template <int D>
+static VisitPChoice visitp_large(int ne) {
+  switch (ne) {
+    case 1: return visitp_choice<D, 1, 4, 1>();
+    case 2: return visitp_choice<D, 1, 4, 2>();
+    case 3: return visitp_choice<D, 4, 1, 3>();
+    default: return visitp_choice<D, 4, 1, 4>();
+  }
+}
+static VisitPChoice visitp_kernel(int D, int ne) {
+  switch (D) {
+    case 2: return visitp_small<2>(ne);
+    case 3: return visitp_small<3>(ne);
+    case 5: return visitp_large<5>(ne);
+    case 6: return visitp_large<6>(ne);
+    default: return VisitPChoice{};
+  }
+}
+static VisitPChoice visitp_tiles(const FitBatch &f) {
+  if (f.d != 2 || f.K > 64) return VisitPChoice{};
+  VisitPChoice c = visitp_kernel(f.D, (f.K + 15) / 16);
+  if (!c.k) return c;
+  // four yf a workgroup: a batch that would leave CUs without a workgroup
+  // splits the xb range (partial Yt in the QR's scratch, P slots of which
+  // the shapes above 32 rows have, summed by k_sum_parts)
+  if (c.TY > 1 && f.t1) {
+    const long sel = f.tile_items > 0 ? f.tile_items : f.items;
+    const long wgs = sel * ((f.K + c.TY - 1) / c.TY);
+    c.nsplit = (int)std::max<long>(1, std::min<long>(std::min(16, f.P), 256 / wgs));
+  }
+  return c;
+}
+
 static hipError_t launch_fused(const FitBatch &f, int c, int j, bool rl, Ptr X,
                                Ptr F, Ptr G, Ptr Y, bool do_local, int TY,
                                int TX, size_t lds, hipStream_t st) {
@@ -3340,6 +3800,12 @@ static hipError_t launch_fused(const FitBatch &f, int c, int j, bool rl, Ptr X,
       for (VisitKernel kf : {visit4_kernel<double>(t.first, t.second),
                              visit4_kernel<float>(t.first, t.second)}) {
         hipError_t e = hipFuncSetAttribute((const void *)kf,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) attr_err = e;
+      }
+    for (int D : {2, 3, 5, 6})
+      for (int ne = 1; ne <= 4; ++ne) {
+        hipError_t e = hipFuncSetAttribute((const void *)visitp_kernel(D, ne).k,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) attr_err = e;
       }
@@ -3396,6 +3862,14 @@ static hipError_t launch_fused(const FitBatch &f, int c, int j, bool rl, Ptr X,
     v.TX = TX4;
     hipLaunchKernelGGL(f32 ? visit4_kernel<float>(TY4, TX4) : visit4_kernel<double>(TY4, TX4),
                        dim3((f.K + TY4 - 1) / TY4, f.items), dim3(kVisitThreads), lds4, st, v);
+  } else if (const VisitPChoice vp = b16 || f32 ? VisitPChoice{} : visitp_tiles(f); vp.k) {
+    v.dims = f.bounded && f.hdims ? f.dims : nullptr;
+    VisitPArgs g{v, vp.nsplit, f.t1, t1_stride(f)};
+    hipLaunchKernelGGL(vp.k, dim3((f.K + vp.TY - 1) / vp.TY * g.nsplit, f.items),
+                       dim3(vp.threads), vp.lds, st, g);
+    if (do_local && g.nsplit > 1)
+      hipLaunchKernelGGL(k_sum_parts, dim3(64, f.items), dim3(kThreads), 0, st, Y,
+                         (const double *)f.t1, t1_stride(f), g.nsplit, (size_t)f.K * f.P * f.K);
   } else {
     const VisitKernel kf = b16   ? visit_kernel<float, true>(f.D)
                            : f32 ? visit_kernel<float>(f.D)

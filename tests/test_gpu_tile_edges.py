@@ -1,9 +1,9 @@
-"""QR/LQ kernels at the edges of their column blocks and row tiles: one
-message update of a 2 x 2 block with Gaussian messages that fill the bond cap,
-so that its inner panels are (chi D^2) x chi, against the FP64 oracle's column
-absorptions.  The bond caps straddle a column block (16, 17, 33, 49), a row
-tile and the change from the one-workgroup kernel (768 x 48) to the one with a
-workgroup per column tile."""
+"""QR/LQ and visit kernels at the edges of their tiles: one message update of
+a small block with Gaussian messages that fill the bond cap, so that its inner
+panels are (chi D^2) x chi, against the FP64 oracle's column absorptions.  The
+bond caps straddle a column block (16, 17, 33, 49), a row tile and the change
+from the one-workgroup QR (768 x 48) to the one with a workgroup per column
+tile."""
 
 import numpy as np
 import pytest
@@ -28,11 +28,15 @@ def _message(rng, n, P, chi):
     (7, 49),                                            # 2401 x 49: one column in the last tile
 ])
 def test_panel_edges(D, chi):
+    _compare(D, 2, 2, chi)
+
+
+def _compare(D, H, W, chi):
     import torch
     from oracle import blockbp as ob
     from paper_2301_05844_amd import bbp
     rng = np.random.default_rng(1000 * D + chi)
-    P, H, W = D * D, 2, 2
+    P = D * D
     A = 0.3 * rng.standard_normal((H * W, 2, D, D, D, D))
     A[:, 0, 0, 0, 0, 0] += 1.0
     sides = [_message(rng, n, P, chi) for n in (W, H, W)]
@@ -53,3 +57,16 @@ def test_panel_edges(D, chi):
     g, r = ob.mps_dense(got), ob.mps_dense(ref)
     assert abs(scale - ls) < TOL
     assert min(np.abs(g - r).max(), np.abs(g + r).max()) < TOL
+
+
+@pytest.mark.parametrize("D,H,chi", [
+    (2, 3, 5), (2, 6, 17), (2, 6, 21), (2, 6, 64),         # X, G tiles of 1, 2, 4 columns
+    (3, 4, 9), (3, 4, 16), (3, 4, 17), (3, 4, 33), (3, 4, 49),
+    (5, 3, 16), (5, 3, 24),                                 # four xb of one yf
+    (5, 4, 33), (5, 4, 37), (6, 4, 33),                     # four yf, the xb range split
+])
+def test_visit_edges(D, H, chi):
+    """Visits at the edges of their tiles: bond caps below, at and above 16
+    columns, rows that leave a tile of yf or xb partly empty, and the split of
+    the xb range over workgroups."""
+    _compare(D, H, 2, chi)
