@@ -1000,6 +1000,10 @@ static bbp_status enqueue_columns(bbp_ctx *c, Group &g, int col_lo, hipStream_t 
   FitBatch &f = g.fb;
   const int W = f.W, N = f.N;
   hipError_t e;
+  if (absorb_small_fits(f)) {
+    e = launch_absorb_small(f, col_hi >= 0 ? col_hi : W - 1, col_lo, c->n_fit, st);
+    return e == hipSuccess ? BBP_OK : c->hip_fail(e, "column absorptions");
+  }
   const size_t sN = (size_t)N * f.S, sWN = (size_t)W * N * f.S;
   for (int col = col_hi >= 0 ? col_hi : W - 1; col >= col_lo; --col) {
     Ptr X = col == W - 1 ? Ptr{f.xin, sN}

@@ -132,6 +132,11 @@ hipError_t launch_inner_local(const FitBatch &f, int c, int j, bool rl, Ptr G,
 // env' = Y . T3 after the visit of site j of column c
 hipError_t launch_inner_env(const FitBatch &f, int c, int j, bool rl, Ptr Y,
                             Ptr envOut, hipStream_t st);
+// Every visit of columns col_hi .. col_lo in one launch, one workgroup per item
+// (small shapes; f.dims holds the bonds and random-start flags).
+bool absorb_small_fits(const FitBatch &f);
+hipError_t launch_absorb_small(const FitBatch &f, int col_hi, int col_lo, int n_fit,
+                               hipStream_t st);
 // End-site chain T = Mend . Xe (top corner in LR, bottom corner in RL).
 hipError_t launch_end_chain(const FitBatch &f, int c, bool rl, Ptr Mend, Ptr Xe,
                             hipStream_t st);

@@ -220,6 +220,16 @@ __device__ __forceinline__ void xcd_tile_item(int *tile, int *item) {
   *tile = slot % nx;
 }
 
+// x of lane Q of the same four lanes
+template <int Q>
+__device__ __forceinline__ double quad_bcast(double x) {
+  constexpr int ctrl = Q | (Q << 2) | (Q << 4) | (Q << 6);  // quad_perm
+  const long long b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_mov_dpp((int)b, ctrl, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), ctrl, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
 // f(integral_constant<int, I>) for I = I0 .. N-1, unrolled at compile time.
 template <int I, int N, class F>
 __device__ __forceinline__ void static_for(F &&f) {
@@ -2740,11 +2750,28 @@ __device__ __forceinline__ Reflector make_reflector(double alpha, double sigma2)
 // partials as one run).
 template <int NW>
 struct QmShared {
-  double wp[2][16][NW + 2], wq[2][16];
+  double wp[2][NW > 1 ? 16 : 1][NW + 2], wq[2][16];
   double G[16][16];   // G[k][c] = v_c^T v_k, c < k
   double T[16][17];   // dlarft's T
   double tau[16];
 };
+
+// Sum of the waves' 16x16 accumulators into Ws (accumulator slots).
+template <int NW>
+__device__ __forceinline__ void qm_reduce(const v4d &acc, double (*wred)[256], double *Ws,
+                                          int tid = threadIdx.x) {
+  const int lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) wred[wave][r * 64 + lane] = acc[r];
+  __syncthreads();
+  if (tid < 256) {
+    double x = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) x += wred[w][tid];
+    Ws[tid] = x;
+  }
+  __syncthreads();
+}
 
 // Factorises a column tile: columns b0 .. b0 + nbb - 1 of the panel, b0 = 16 b
 // (b < NW, so that the diagonal lies in row tile t = 0 of wave b), reflectors
@@ -2757,15 +2784,22 @@ struct QmShared {
 // and entry give dlarfg; w_c = a_kc + scal x^T a_c gives dlarf's update of
 // the later columns, and for the earlier ones (their reflectors, not yet
 // scaled) the entry v_c^T v_k = scal_c w_c of V^T V that T is made from, so
-// no pass over V is spent on it.
+// no pass over V is spent on it.  A block with a zero reflector (a column that
+// vanishes below its diagonal) takes V^T V from the scaled V instead: such
+// panels have rows or columns that are exactly zero (single-layer networks,
+// trivial legs), which Q keeps only where T agrees with V bit for bit; the
+// leftovers of 1e-16 would otherwise be normalised to full columns by the next
+// site's factorisation.
 //
 // Bound by the dependent chain of a step (one barrier, two sums over the row
 // groups, dlarfg).  After the barrier a lane reads the partials of NW / 4
 // waves and the row groups' sums meet in registers: reading all NW partials
 // of its own and of column k in every lane (18 reads per lane and wave) kept
-// the LDS port busy for 576 cycles of a step's 1400.
+// the LDS port busy for 576 cycles of a step's 1400.  A panel of one wave (NW
+// = 1) needs neither LDS nor a barrier in a step.
 template <int NW, int RT>
 __device__ __forceinline__ void qm_factor(v4d (&a)[RT], int b, int nbb, QmShared<NW> &sh,
+                                          double (*wred)[256], double *Ws,
                                           int tid = threadIdx.x) {
   const int lane = tid & 63, wave = tid >> 6;
   const int lr = lane >> 4, lc = lane & 15, b0 = 16 * b;
@@ -2785,7 +2819,7 @@ __device__ __forceinline__ void qm_factor(v4d (&a)[RT], int b, int nbb, QmShared
       if (r0 + 4 * s <= kc) x0[s] = 0.0;
       pp[s] = x0[s] * a[0][s];
     }
-    if (r0 == (kc & 3)) sh.wq[pb][lc] = a[0][kc >> 2];  // the lanes of row k
+    if (NW > 1 && r0 == (kc & 3)) sh.wq[pb][lc] = a[0][kc >> 2];  // the lanes of row k
 #pragma unroll
     for (int t = 1; t < RT; ++t)
 #pragma unroll
@@ -2795,13 +2829,19 @@ __device__ __forceinline__ void qm_factor(v4d (&a)[RT], int b, int nbb, QmShared
         pp[s] = fma(x, a[t][s], pp[s]);
       }
     const double pdot = sum_rows4((pp[0] + pp[1]) + (pp[2] + pp[3]));
-    if (lr == 0) sh.wp[pb][lc][wave] = pdot;
-    __syncthreads();
-    double part = sh.wp[pb][lc][lr * (NW / 4)];
-    const double qc = sh.wq[pb][lc];
+    double pc, qc;
+    if constexpr (NW > 1) {
+      if (lr == 0) sh.wp[pb][lc][wave] = pdot;
+      __syncthreads();
+      double part = sh.wp[pb][lc][lr * (NW / 4)];
+      qc = sh.wq[pb][lc];
 #pragma unroll
-    for (int i = 1; i < NW / 4; ++i) part += sh.wp[pb][lc][lr * (NW / 4) + i];
-    const double pc = sum_rows4(part);
+      for (int i = 1; i < NW / 4; ++i) part += sh.wp[pb][lc][lr * (NW / 4) + i];
+      pc = sum_rows4(part);
+    } else {
+      pc = pdot;
+      qc = sum_rows4(lr == (kc & 3) ? a[0][kc >> 2] : 0.0);
+    }
     const Reflector h = make_reflector(row_bcast<kc>(qc), row_bcast<kc>(pc));
     const double w = fma(h.scal, pc, qc);
     if (wave == 0 && lr == 0 && lc < kc) sh.G[kc][lc] = my_scal * w;
@@ -2841,6 +2881,27 @@ __device__ __forceinline__ void qm_factor(v4d (&a)[RT], int b, int nbb, QmShared
         }
       }
   }
+  if (__ballot(lc < nbb && my_tau == 0.0) != 0) {  // the same in every wave
+    v4d acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int d = 16 * (wave + NW * t) + 4 * s + lr - b0 - lc;
+        const double x = lc < nbb ? (d > 0 ? a[t][s] : (d == 0 ? 1.0 : 0.0)) : 0.0;
+        acc[s & 1] = mfma16(x, x, acc[s & 1]);
+      }
+    acc[0] += acc[1];
+    if constexpr (NW > 1) {
+      qm_reduce<NW>(acc[0], wred, Ws, tid);
+      if (wave == 0)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc[0][s] = Ws[s * 64 + lane];
+    }
+    if (wave == 0)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) sh.G[lc][4 * s + lr] = acc[0][s];
+  }
   // T as in dlarft (forward, columnwise), by the wave that holds G: lane
   // (lr, lc) keeps T[lc][lr + 4u]; column i of T needs columns < i
   if (wave == 0) {
@@ -2849,11 +2910,12 @@ __device__ __forceinline__ void qm_factor(v4d (&a)[RT], int b, int nbb, QmShared
     double tr[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const double ti = i < nbb ? sh.tau[i] : 0.0;
+      if (i >= nbb) continue;
+      const double ti = sh.tau[i];
       double x = 0.0;
 #pragma unroll
       for (int u = 0; u < 4; ++u)
-        if (4 * u < i && lr + 4 * u < i && i < nbb) x += tr[u] * sh.G[i][lr + 4 * u];
+        if (4 * u < i && lr + 4 * u < i) x += tr[u] * sh.G[i][lr + 4 * u];
       x = sum_rows4(x);
       const double t = lc < i ? -ti * x : (lc == i ? ti : 0.0);
       if (lr == (i & 3)) tr[i >> 2] = t;
@@ -2901,53 +2963,42 @@ __device__ __forceinline__ QrPanel qr_panel(const QrArgs &q, int it) {
   return p;
 }
 
-// Sum of the waves' 16x16 accumulators into Ws (accumulator slots).
-template <int NW>
-__device__ __forceinline__ void qm_reduce(const v4d &acc, double (*wred)[256], double *Ws,
-                                          int tid = threadIdx.x) {
-  const int lane = tid & 63, wave = tid >> 6;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) wred[wave][r * 64 + lane] = acc[r];
-  __syncthreads();
-  if (tid < 256) {
-    double x = 0.0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) x += wred[w][tid];
-    Ws[tid] = x;
-  }
-  __syncthreads();
-}
-
 // -op(T) W as the update's MFMA B operands (register s: row 4s + lr, column
-// lc), every wave for itself: no second pass through LDS.
-__device__ __forceinline__ v4d qm_coeff(const double (*T)[17], bool trans, const double *Ws,
-                                        int lr, int lc) {
+// lc), every wave for itself: no second pass through LDS.  w(q) is W[q][lc].
+template <class F>
+__device__ __forceinline__ v4d qm_coeff(const double (*T)[17], bool trans, F &&w, int lr, int lc) {
   v4d z = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
   for (int s = 0; s < 4; ++s)
-    z = mfma16(trans ? T[4 * s + lr][lc] : T[lc][4 * s + lr], Ws[s * 64 + lr * 16 + lc], z);
+    z = mfma16(trans ? T[4 * s + lr][lc] : T[lc][4 * s + lr], w(4 * s + lr), z);
   return -z;
 }
 
 // LDS of a panel's factorisation in one workgroup.
 template <int NW, int RT, int CT>
 struct QmBuf {
-  static constexpr int VS = 16 * NW * RT + 16;
+  // a multiple of 32 rows, + 16: the stride is 16 (mod 32)
+  static constexpr int VS = (16 * NW * RT + 31) / 32 * 32 + 16;
   double VT[16 * VS];  // V of the current block, column c at qm_col(c)
   double wred[NW][256];
   double Ws[256];
   QmShared<NW> sh[CT];
 };
 
-// QR of a panel held in registers by one workgroup of NW waves: a[ct][t]
+// QR of a panel held in registers by NW waves (the whole workgroup, or with
+// NW = 1 its first wave alone): a[ct][t]
 // register s of lane (lr, lc) is row 16 (wave + NW t) + 4 s + lr, column 16 ct
 // + lc, zero outside the n columns and the true rows.  on_r() is called with R
 // on and above a's diagonal; then a becomes Q.
 template <int NW, int RT, int CT, class F>
 __device__ __forceinline__ void qm_panel(v4d (&a)[CT][RT], int n, QmBuf<NW, RT, CT> &sm,
                                          F &&on_r, int tid = threadIdx.x) {
-  static_assert(NW % 4 == 0 && NW >= CT, "panel shape");
+  static_assert((NW % 4 == 0 && NW >= CT) || (NW == 1 && CT == 1), "panel shape");
   constexpr int VS = QmBuf<NW, RT, CT>::VS;
+  auto sync = [&]() __attribute__((always_inline)) {  // of the NW waves
+    if constexpr (NW > 1) __syncthreads();
+    else wave_lds_order();
+  };
   const int lane = tid & 63, wave = tid >> 6;
   const int lr = lane >> 4, lc = lane & 15;
   double *VT = sm.VT, *Ws = sm.Ws;
@@ -2987,7 +3038,7 @@ __device__ __forceinline__ void qm_panel(v4d (&a)[CT][RT], int n, QmBuf<NW, RT, 
         for (int s = 0; s < 4; ++s)
           acc[s & 1] = mfma16(vent(b, nbb, t, s), a[ct][t][s], acc[s & 1]);
       qm_reduce<NW>(acc[0] + acc[1], sm.wred, Ws, tid);  // W = V^T C
-      update_tile(a[ct], qm_coeff(sm.sh[b].T, trans, Ws, lr, lc));
+      update_tile(a[ct], qm_coeff(sm.sh[b].T, trans, [&](int q) { return Ws[cl_index(q, lc)]; }, lr, lc));
     }
   };
 
@@ -2996,7 +3047,7 @@ __device__ __forceinline__ void qm_panel(v4d (&a)[CT][RT], int n, QmBuf<NW, RT, 
     constexpr int b = decltype(B)::value;
     if (16 * b >= n) return;
     const int nbb = min(16, n - 16 * b);
-    qm_factor<NW, RT>(a[b], b, nbb, sm.sh[b], tid);
+    qm_factor<NW, RT>(a[b], b, nbb, sm.sh[b], sm.wred, Ws, tid);
     if (b + 1 < CT && 16 * (b + 1) < n) {
       store_v(b, nbb);
       apply_block(b, nbb, true);
@@ -3010,22 +3061,19 @@ __device__ __forceinline__ void qm_panel(v4d (&a)[CT][RT], int n, QmBuf<NW, RT, 
     constexpr int b = CT - 1 - decltype(B)::value, b0 = 16 * b;
     if (b0 >= n) return;
     const int nbb = min(16, n - b0);
-    __syncthreads();  // the previous block's V is no longer read
+    sync();  // the previous block's V is no longer read
     store_v(b, nbb);
     apply_block(b, nbb, false);
-    __syncthreads();  // V of every wave (and T) visible
+    sync();  // V of every wave (and T) visible
     // the block's own columns: E - V (T V_top^T), E the unit columns at rows b0..
-    v4d z = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-      z = mfma16(sm.sh[b].T[lc][4 * s + lr], VT[qm_col<VS>(4 * s + lr) + b0 + lc], z);
+    const v4d z = qm_coeff(sm.sh[b].T, false, [&](int q) { return VT[qm_col<VS>(q) + b0 + lc]; }, lr, lc);
     v4d c[RT];
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
       for (int s = 0; s < 4; ++s)
         c[t][s] = (t == 0 && rowof(0, s) == b0 + lc && lc < nbb) ? 1.0 : 0.0;
-    update_tile(c, -z);
+    update_tile(c, z);
 #pragma unroll
     for (int t = 0; t < RT; ++t) a[b][t] = c[t];
   });
@@ -3179,10 +3227,10 @@ struct QrbTile {
   }
   // C -= V op(T) (V^T C)
   __device__ __forceinline__ void apply(v4d (&c)[RT], const double *scr, int b, int nbb, int MT,
-                                        bool trans, const double *Tg, double (*T)[17],
+                                        bool trans, const double *Tg, QmShared<NW> &sh,
                                         double (*wred)[256], double *Ws,
                                         double (*tr)[16][17]) const {
-    if (threadIdx.x < 256) T[threadIdx.x >> 4][threadIdx.x & 15] = gmem(Tg)[threadIdx.x];
+    if (threadIdx.x < 256) sh.T[threadIdx.x >> 4][threadIdx.x & 15] = gmem(Tg)[threadIdx.x];
     v4d acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
@@ -3193,7 +3241,8 @@ struct QrbTile {
       for (int s = 0; s < 4; ++s) acc[s & 1] = mfma16(v[s], c[t][s], acc[s & 1]);
     }
     qm_reduce<NW>(acc[0] + acc[1], wred, Ws);
-    update(c, scr, b, nbb, MT, qm_coeff(T, trans, Ws, lr, lc), tr);
+    update(c, scr, b, nbb, MT,
+           qm_coeff(sh.T, trans, [&](int q) { return Ws[cl_index(q, lc)]; }, lr, lc), tr);
     __syncthreads();  // T and Ws are refilled by the next block
   }
 };
@@ -3242,10 +3291,10 @@ __global__ __launch_bounds__(kQrbWaves * 64) void k_qrb_factor(QrbArgs g) {
                       ? gmem(scr)[((size_t)c * g.MT + w.rtile(t)) * 256 + s * 64 + w.lane]
                       : 0.0;
   }
-  if (b > 0) w.apply(a, scr, b - 1, 16, g.MT, true, Tg + (b - 1) * 256, sh.T, wred, Ws, tr[w.wave]);
+  if (b > 0) w.apply(a, scr, b - 1, 16, g.MT, true, Tg + (b - 1) * 256, sh, wred, Ws, tr[w.wave]);
   const int nbb = min(16, n - 16 * b);
   if (c == b) {
-    qm_factor<NW, RT>(a, b, nbb, sh);
+    qm_factor<NW, RT>(a, b, nbb, sh, wred, Ws);
     if (w.wave == 0) {
       wave_lds_order();
 #pragma unroll
@@ -3281,7 +3330,8 @@ __global__ __launch_bounds__(kQrbWaves * 64) void k_qrb_q(QrbArgs g) {
   const QrPanel pn = qr_panel(q, it);
   const int K = q.K, m = pn.m, n = pn.n;
   if (16 * c >= n) return;
-  __shared__ double T[16][17], wred[NW][256], Ws[256];
+  __shared__ QmShared<NW> sh;
+  __shared__ double wred[NW][256], Ws[256];
   __shared__ double tr[NW][2][16][17];
   const QrbTile<RT> w(m);
   const double *scr = q.scratch + (size_t)it * q.scratch_stride;
@@ -3294,17 +3344,16 @@ __global__ __launch_bounds__(kQrbWaves * 64) void k_qrb_q(QrbArgs g) {
     for (int s = 0; s < 4; ++s)
       a[t][s] = (t == 0 && 16 * (w.wave - c) + 4 * s + w.lr == w.lc && w.lc < nbb) ? 1.0 : 0.0;
   // the block's own columns: E - V (T V_top^T)
-  v4d z = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const int k = 4 * s + w.lr;  // V_top[lc][k]
-    double v = gmem(scr)[((size_t)c * g.MT + c) * 256 + cl_index(w.lc, k)];
-    v = k < nbb ? (w.lc > k ? v : (w.lc == k ? 1.0 : 0.0)) : 0.0;
-    z = mfma16(gmem(Tg)[c * 256 + w.lc * 16 + k], v, z);
-  }
-  w.update(a, scr, c, nbb, g.MT, -z, tr[w.wave]);
+  if (threadIdx.x < 256) sh.T[threadIdx.x >> 4][threadIdx.x & 15] = gmem(Tg)[c * 256 + threadIdx.x];
+  __syncthreads();
+  const v4d z = qm_coeff(sh.T, false, [&](int k) {  // V_top[lc][k]
+    const double v = gmem(scr)[((size_t)c * g.MT + c) * 256 + cl_index(w.lc, k)];
+    return k < nbb ? (w.lc > k ? v : (w.lc == k ? 1.0 : 0.0)) : 0.0;
+  }, w.lr, w.lc);
+  __syncthreads();  // T is refilled by the next block
+  w.update(a, scr, c, nbb, g.MT, z, tr[w.wave]);
   for (int b = c - 1; b >= 0; --b)
-    w.apply(a, scr, b, 16, g.MT, false, Tg + b * 256, T, wred, Ws, tr[w.wave]);
+    w.apply(a, scr, b, 16, g.MT, false, Tg + b * 256, sh, wred, Ws, tr[w.wave]);
   const unsigned ybytes = (unsigned)(K * q.P * K) * 8u;
   const __amdgpu_buffer_rsrc_t yrs = buf_rsrc(q.Y.at(it), ybytes);
   const DivN dn2(pn.n2);
@@ -3355,6 +3404,434 @@ __global__ __launch_bounds__(kThreads) void k_rand_init(
     else if (j == N - 1) addr = (size_t)y0 * K + a;      // [bl][p]
     else addr = ((size_t)y0 * P + a) * K + y1;           // [bl][p][br]
     y[addr] = u;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Column absorptions of small shapes in one launch (D = 2, d = 2, bond caps up
+// to 20): one workgroup of four waves per item runs every visit of columns
+// col_hi .. col_lo - random start, right environments, the n_fit sweeps, the
+// final centre and its norm - with the visit's operands in LDS.  Launched one
+// by one these visits are three kernels of 4 to 8 us of which the arithmetic
+// is a fraction (K = 8: 0.2 MFLOP), so the chain of launches bounded them:
+// one message update of a 2x2 block at chi = 4 was 130 launches.
+//
+// A visit: four lanes per (yf, xb) pair contract F, X, ket and bra in registers
+// (T1, T2, T3 are 4 x 4 each; a lane makes a row of T1, passes it round the
+// quad and takes one column (lk, wbk) of the ket's output through the bra) and
+// leave T3 in LDS as [(yf, l)][(xb, wb)]; the local update Yt = T3 G on MFMA
+// lands in the QR's register layout (RL visits read T3's rows in the order
+// (l, yf) of their panel); the QR is qm_panel, up to K = 8 by one wave, whose
+// steps then need no barrier; and env' = Q^T T3 on MFMA is the next visit's F,
+// in LDS, and goes to memory for the sweep back.  The end sites are the same
+// with T[a][(xb, q)] in place of T3.  X, G, the site tensor (or an end site's
+// message) of the next visit are fetched into registers before the QR.  An end
+// visit's G is the environment just computed.
+//
+// All loops stop at the item's true bonds.  LDS at bond cap K: T3 (4 K)^2
+// doubles and the QR's buffers, which leaves room up to K = 20.
+//
+// Bound by the chain of a visit: 4.8 us at K = 4 (a 2x2 block's 8 messages of
+// one sweep 153 us, against 480 us of launches of which each waited for the
+// one before), 12 us at K = 18.
+// ---------------------------------------------------------------------------
+struct SmallArgs {
+  FitBatch f;
+  int col_lo, col_hi, n_fit;
+};
+
+// QW waves factorise: 1 up to K = 8 (32 rows), else all four
+template <int CT, int QW>
+struct SmallShape {
+  static constexpr int P = 4, NW = 4, NT = 64 * NW, RT = QW == 1 ? 2 : CT;
+  static constexpr int QS = CT == 1 ? 16 : 48;  // row stride of Q and G: 16 (mod 32)
+  typedef QmBuf<QW, RT, CT> Qm;
+  // K P K / NT elements a thread
+  static constexpr int NPF = QW == 1 ? 1 : CT == 1 ? 4 : 7;
+  // row stride of T3: 18 (mod 32), conflict-free as the A operand of the local
+  // update (16 rows, 4 k) and nearly so as the B operand of env'
+  static __host__ __device__ int ld3(int K) { return P * K + (50 - P * K % 32) % 32; }
+  static __host__ __device__ int fst(int K) { return P * K + 1; }
+  static __host__ __device__ size_t words(int K) {
+    const size_t qm = sizeof(Qm) / 8, q = (size_t)(P * K + 4) * QS + 64;
+    return (size_t)P * K * ld3(K) + 64 + (size_t)P * K * QS + (size_t)K * fst(K) +
+           (size_t)K * P * K + 64 + (qm > q ? qm : q);
+  }
+};
+
+template <int CT, int QW>
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(CT == 1 ? 2 : 1))) void k_absorb_small(SmallArgs g) {
+  typedef SmallShape<CT, QW> Sh;
+  constexpr int P = Sh::P, NT = Sh::NT, NW = Sh::NW, RT = Sh::RT, QS = Sh::QS, NPF = Sh::NPF;
+  extern __shared__ double sm_raw[];
+  __shared__ double As[64];  // ket, then bra: front view [s][wf, a][l, wb]
+  __shared__ double red[NW];
+  __shared__ FitDims dm;
+  const FitBatch &f = g.f;
+  const int K = f.K, N = f.N, W = f.W, KPK = K * P * K, it = blockIdx.x;
+  const int LD = Sh::ld3(K), FS = Sh::fst(K);
+  int tid = threadIdx.x;
+  double *T3 = sm_raw;                     // [(yf, l)][(xb, wb)]
+  double *Gs = T3 + P * K * LD + 64;       // [(xb, wb)][yb]
+  double *Fs = Gs + P * K * QS;            // [yf][wf][xf]; an end site's message [a][q][a']
+  double *Xs = Fs + K * FS;                // [xf][a][xb]; an end site's X [a'][xb]
+  auto &qm = *reinterpret_cast<typename Sh::Qm *>(Xs + KPK + 64);
+  double *Qs = Xs + KPK + 64;              // [(yf, l)][yb], after the QR is done with its LDS
+  const DivN dK(K);
+  const size_t S = f.S;
+  double *store = f.store + (size_t)it * W * N * S;
+  double *lenv = f.lenv + (size_t)it * N * S, *renv = f.renv + (size_t)it * N * S;
+  auto zero_tiles = [&](v4d (&a)[CT][RT]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+      for (int t = 0; t < RT; ++t) a[ct][t] = v4d{0.0, 0.0, 0.0, 0.0};
+  };
+
+  for (int col = g.col_hi; col >= g.col_lo; --col) {
+    __syncthreads();  // the previous column's reads of dm and its stores
+    {
+      const int *src = reinterpret_cast<const int *>(f.dims + (size_t)it * W + col);
+      int *dst = reinterpret_cast<int *>(&dm);
+      for (int i = tid; i < (int)(sizeof(FitDims) / 4); i += NT) dst[i] = src[i];
+    }
+    __syncthreads();
+    double *Y = store + (size_t)col * N * S;
+    const double *X = col == W - 1 ? f.xin + (size_t)it * N * S : Y + (size_t)N * S;
+    const double *MT = f.mt + ((size_t)it * W + col) * S, *MB = f.mb + ((size_t)it * W + col) * S;
+
+    const uint64_t h0 = splitmix(splitmix(f.seed) ^ (f.slot[it] + col));
+    if (dm.rnd)
+      for (int i = tid; i < N * (int)S; i += NT) Y[i] = 0.0;
+
+    // Visits of the column in order: with a random start, sites N - 1 .. 1 of it
+    // brought to right-canonical form (v < 0); N - 1 right environments (site
+    // N - 1 .. 1), then n_fit times left to right (0 .. N - 2) and right to
+    // left (N - 1 .. 1), then the final centre at site 0.
+    const int nv = (N - 1) * (1 + 2 * g.n_fit) + 1;
+    auto visit = [&](int v, int &j, bool &rl, int &mode) __attribute__((always_inline)) {
+      if (v < 0) {
+        j = -v;
+        rl = true;
+        mode = 3;
+        return;
+      }
+      if (v == nv - 1) {
+        j = 0;
+        rl = false;
+        mode = 2;
+        return;
+      }
+      const int sweep = v / (N - 1), k = v - sweep * (N - 1);
+      rl = (sweep & 1) == 0;
+      j = rl ? N - 1 - k : k;
+      mode = sweep == 0 ? 0 : 1;  // 0 environment only, 1 fit, 2 final, 3 start
+    };
+    double xr[NPF], gr[NPF], mr[NPF], yr[NPF], ar = 0.0;
+    auto fetch = [&](int v) __attribute__((always_inline)) {
+      int j, mode;
+      bool rl;
+      visit(v, j, rl, mode);
+      const bool end = j == 0 || j == N - 1;
+      const double *x = X + (size_t)j * S;
+      const double *gsrc = (rl ? lenv : renv) + (size_t)j * S;
+      const double *msrc = rl ? MB : MT;
+#pragma unroll
+      for (int u = 0; u < NPF; ++u) {
+        const int e = tid + NT * u;
+        xr[u] = e < (end ? K * K : KPK) ? gmem(x)[e] : 0.0;
+        gr[u] = mode > 0 && !end && e < KPK ? gmem(gsrc)[e] : 0.0;
+        mr[u] = end && e < KPK ? gmem(msrc)[e] : 0.0;
+        // environment-only visits read the site's current tensor
+        yr[u] = mode == 0 && e < (end ? K * K : KPK) ? gmem(Y)[(size_t)j * S + e] : 0.0;
+      }
+      if (!end && tid < 64) {  // site tensors in the front view: ket, then bra
+        const size_t site = (((size_t)it * f.H + (j - 1)) * W + col) * 32;
+        const double *src = tid < 32      ? f.acan + site
+                            : f.bra_one   ? f.bra_one
+                                          : (f.abra ? f.abra : f.acan) + site;
+        const int wb = tid & 1, l = (tid >> 1) & 1, a = (tid >> 2) & 1, wf = (tid >> 3) & 1,
+                  s = (tid >> 4) & 1;
+        ar = src[(((s * 2 + (rl ? wb : wf)) * 2 + l) * 2 + (rl ? wf : wb)) * 2 + a];
+      }
+    };
+    const int v0 = dm.rnd ? 1 - N : 0;
+    if (v0 == 0) fetch(0);
+    for (int v = v0; v < nv; ++v) {
+      // opaque: the lane's offsets are formed in each visit instead of held in
+      // registers across all of them
+      asm volatile("" : "+v"(tid));
+      const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+      const int lr = lane & 15, lq = lane >> 4;
+      int j, mode;
+      bool rl;
+      visit(v, j, rl, mode);
+      const bool end = j == 0 || j == N - 1;
+      const SiteExt ex = site_ext(dm, j, N, rl);
+      // end sites: rows a of the message site, back bonds of Y and X
+      const int nyf = end ? 1 : ex.yf, nyb = ex.yb, nxf = ex.xf, nxb = ex.xb;
+      const int M = end ? dm.p[j] : nyf * P, Nn = nxb * P;
+      v4d a[CT][RT];
+      int nat[RT][4];  // T3 row of panel row 16 (wave + NW t) + 4 s + lq
+      const int n = min(nyb, M);
+      if (mode == 3) {
+        // counter-based random site (k_rand_init): its panel, rows (l, y') and
+        // columns the left bond, times the R of the next site (in Xs); Q
+        // replaces the site and R goes on to the one before.  Site 0 is not
+        // made: the first visit that reads it has written it.
+        const int p = dm.p[j], br = dm.br[j], bl = dm.bl[j];
+        const uint64_t h = splitmix(h0 ^ (uint64_t)j);
+        for (int i = tid; i < bl * p * br; i += NT)
+          Fs[i] = (double)(splitmix(h ^ (uint64_t)i) >> 11) * 0x1p-52 - 1.0;  // U [bl][p][br]
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const int row = min(16 * (wave + QW * t) + 4 * s + lq, M - 1);
+            const int l = row / br, y = row - l * br;
+            nat[t][s] = end ? row : y * P + l;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+              const int c = 16 * ct + lr;
+              double x = 0.0;
+              if (wave < QW && 16 * (wave + QW * t) + 4 * s + lq < M && c < n) {
+                const double *u = Fs + (c * p + l) * br;
+                if (end) x = u[y];
+                else
+                  for (int k = y; k < br; ++k) x = fma(u[k], Xs[y * K + k], x);
+              }
+              a[ct][t][s] = x;
+            }
+          }
+        __syncthreads();  // Xs is read
+      } else {
+        // an end visit's G is the environment the previous visit left in Fs
+        if (end && mode > 0) {
+          for (int i = tid; i < nyb * Nn; i += NT) {
+            const int yb = i / Nn, n = i - yb * Nn;
+            Gs[n * QS + yb] = Fs[yb * FS + (n & 3) * K + (n >> 2)];
+          }
+          __syncthreads();
+        }
+#pragma unroll
+        for (int u = 0; u < NPF; ++u) {
+          const int e = tid + NT * u;
+          if (end) {
+            if (e < K * K) {
+              const int i0 = dK.quot(e), i1 = e - i0 * K;
+              Xs[rl ? i1 * K + i0 : e] = xr[u];
+            }
+            if (e < KPK) Fs[e] = mr[u];
+          } else if (e < KPK) {
+            const int q = dK.quot(e), i1 = e - q * K, a = q & 3, i0 = q >> 2;
+            Xs[rl ? (i1 * P + a) * K + i0 : e] = xr[u];
+            if (mode > 0) Gs[(i1 * P + a) * QS + i0] = gr[u];
+          }
+        }
+        if (!end && tid < 64) As[tid] = ar;
+        if (mode == 0) {  // the site as Q
+#pragma unroll
+          for (int u = 0; u < NPF; ++u) {
+            const int e = tid + NT * u;
+            if (e >= (end ? K * K : KPK)) continue;
+            const int q = dK.quot(e), i1 = e - q * K;
+            if (end) {  // Y [yb][a]
+              if (i1 < M) Qs[i1 * QS + q] = yr[u];
+            } else if (i1 < nyf) {  // Y [yb][l][yf]
+              Qs[(i1 * P + (q & 3)) * QS + (q >> 2)] = yr[u];
+            }
+          }
+        }
+        __syncthreads();
+        // ---- T3 --------------------------------------------------------------
+        if (end) {  // T[a][xb][q] = sum_a' M[a][q][a'] X[a'][xb]
+          const int na = dm.p[j];
+          const int ap = col == W - 1 ? 1 : f.dims[(size_t)it * W + col + 1].p[j];
+          for (int i = tid; i < na * nxb; i += NT) {
+            const int a = i / nxb, xb = i - a * nxb;
+            double t[P] = {0.0, 0.0, 0.0, 0.0};
+            for (int k = 0; k < ap; ++k) {
+              const double x = Xs[k * K + xb];
+#pragma unroll
+              for (int q = 0; q < P; ++q) t[q] = fma(Fs[(a * P + q) * K + k], x, t[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < P; ++q) T3[a * LD + xb * P + q] = t[q];
+          }
+        } else {
+          for (int i = tid; i < nyf * nxb * 4; i += NT) {
+            const int q = i & 3, pr = i >> 2, yf = pr / nxb, xb = pr - yf * nxb;
+            double t1[P][P];  // [wf][a]; this lane's row wf = q first
+            double tq[P] = {0.0, 0.0, 0.0, 0.0};
+            const double *pf = Fs + yf * FS + q * K, *px = Xs + xb;
+#pragma unroll 4
+            for (int k = nxf - 1; k >= 0; --k) {
+              const double fv = pf[k];
+#pragma unroll
+              for (int a = 0; a < P; ++a) tq[a] = fma(fv, px[(k * P + a) * K], tq[a]);
+            }
+#pragma unroll
+            for (int a = 0; a < P; ++a) {
+              t1[0][a] = quad_bcast<0>(tq[a]);
+              t1[1][a] = quad_bcast<1>(tq[a]);
+              t1[2][a] = quad_bcast<2>(tq[a]);
+              t1[3][a] = quad_bcast<3>(tq[a]);
+            }
+            double t3[P] = {0.0, 0.0, 0.0, 0.0};  // (lb, wbb) of column q = (lk, wbk)
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+              double t2[P] = {0.0, 0.0, 0.0, 0.0};  // (wfb, ab)
+#pragma unroll
+              for (int k = 0; k < P; ++k) {  // (wfk, ak)
+                const double b = As[(s * P + k) * P + q];
+#pragma unroll
+                for (int m = 0; m < P; ++m)
+                  t2[m] = fma(t1[(k >> 1) * 2 + (m >> 1)][(k & 1) * 2 + (m & 1)], b, t2[m]);
+              }
+#pragma unroll
+              for (int k = 0; k < P; ++k)  // (wfb, ab)
+#pragma unroll
+                for (int n = 0; n < P; ++n)
+                  t3[n] = fma(t2[k], As[32 + (s * P + k) * P + n], t3[n]);
+            }
+#pragma unroll
+            for (int n = 0; n < P; ++n)  // l = (lk, lb), wb = (wbk, wbb)
+              T3[(yf * P + (q >> 1) * 2 + (n >> 1)) * LD + xb * P + (q & 1) * 2 + (n & 1)] = t3[n];
+          }
+        }
+        if (v + 1 < nv) fetch(v + 1);
+        __syncthreads();
+        if (mode != 0 && wave < QW) {
+          // ---- Yt in the panel's register layout -------------------------------
+          zero_tiles(a);
+#pragma unroll
+          for (int t = 0; t < RT; ++t) {
+            const int m0 = 16 * (wave + QW * t);
+            auto natural = [&](int m) __attribute__((always_inline)) {
+              if (end || !rl) return m;
+              const int l = m / nyf;
+              return (m - l * nyf) * P + l;  // rows (l, yf)
+            };
+#pragma unroll
+            for (int s = 0; s < 4; ++s) nat[t][s] = natural(min(m0 + 4 * s + lq, M - 1));
+            if (m0 >= M) continue;
+            const double *pa = T3 + natural(min(m0 + lr, M - 1)) * LD + lq;
+            const double *pb = Gs + lq * QS + lr;
+            for (int k = 0; k < Nn; k += 4) {
+              const double x = pa[k];
+#pragma unroll
+              for (int ct = 0; ct < CT; ++ct)
+                a[ct][t] = mfma16(x, pb[k * QS + 16 * ct], a[ct][t]);
+            }
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+              for (int s = 0; s < 4; ++s)
+                if (m0 + 4 * s + lq >= M || 16 * ct + lr >= (mode == 2 ? nyb : n)) a[ct][t][s] = 0.0;
+          }
+        }
+        if (mode == 2) {  // the final centre, scaled to unit norm
+          if (wave < QW) {
+            double part = 0.0;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+              for (int t = 0; t < RT; ++t)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) part = fma(a[ct][t][s], a[ct][t][s], part);
+            part = wave_sum(part);
+            if (lane == 0) red[wave] = part;
+          }
+          __syncthreads();
+          double ss = red[0];
+#pragma unroll
+          for (int w = 1; w < QW; ++w) ss += red[w];
+          const double nrm = sqrt(ss);
+          const bool ok = nrm > 0.0 && isfinite(nrm);
+          if (tid == 0) {
+            f.nu[(size_t)it * W + col] = nrm;
+            if (!ok) atomicOr(f.err, 1);
+          }
+          const double inv = ok ? 1.0 / nrm : 1.0;
+          if (wave < QW) {
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+              for (int t = 0; t < RT; ++t)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                  const int row = 16 * (wave + QW * t) + 4 * s + lq, c = 16 * ct + lr;
+                  if (row < M && c < nyb) Y[row * K + c] = a[ct][t][s] * inv;
+                }
+          }
+          break;
+        }
+      }
+      if (mode != 0 && wave < QW) {
+        qm_panel<QW, RT, CT>(a, n, qm, [&]() __attribute__((always_inline)) {
+          if (mode != 3) return;
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+              const int row = 16 * wave + 4 * s + lq, c = 16 * ct + lr;
+              if (row < n && c < n) Xs[row * K + c] = c >= row ? a[ct][0][s] : 0.0;
+            }
+        }, tid);
+        if constexpr (QW > 1) __syncthreads();  // the QR's LDS is free
+        else wave_lds_order();
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const int row = 16 * (wave + QW * t) + 4 * s + lq;
+            if (row >= M) continue;
+            const int r = nat[t][s];
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+              const int c = 16 * ct + lr;
+              Qs[r * QS + c] = a[ct][t][s];
+              if (c >= n) continue;
+              // LR: [row][yb]; RL: end [yb][a], inner [yb][l][yf]
+              const size_t o = !rl ? (size_t)row * K + c
+                                   : (end ? (size_t)c * K + row
+                                          : (size_t)(c * P + (r & 3)) * K + (r >> 2));
+              Y[(size_t)j * S + o] = a[ct][t][s];
+            }
+          }
+      }
+      if (v == -1) fetch(0);
+      __syncthreads();
+      if (mode == 3) continue;
+      // ---- env'[yb][(xb, wb)] = sum_rows Q[row][yb] T3[row][(xb, wb)] ---------
+      {
+        const int tm = (nyb + 15) >> 4, tn = (Nn + 15) >> 4;
+        const int jn = rl ? j - 1 : j + 1;
+        double *E = (rl ? renv : lenv) + (size_t)jn * S;
+        const bool keep = jn > 0 && jn < N - 1;  // read again by the sweep back
+        for (int i = wave; i < tm * tn; i += NW) {
+          const int m0 = (i / tn) << 4, n0 = (i % tn) << 4;
+          const double *pa = Qs + lq * QS + m0 + lr, *pb = T3 + lq * LD + n0 + lr;
+          v4d e = {0.0, 0.0, 0.0, 0.0};
+          for (int k = 0; k < M; k += 4) {
+            const bool in = k + lq < M;
+            e = mfma16(in ? pa[k * QS] : 0.0, in ? pb[k * LD] : 0.0, e);
+          }
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const int m = m0 + 4 * s + lq, n = n0 + lr;
+            if (m < nyb && n < Nn) {
+              const int o = (n & 3) * K + (n >> 2);
+              Fs[m * FS + o] = e[s];
+              if (keep) E[m * P * K + o] = e[s];
+            }
+          }
+        }
+      }
+      __syncthreads();
+    }
   }
 }
 
@@ -4111,6 +4588,60 @@ hipError_t launch_qr(const FitBatch &f, int c, int j, int mode, Ptr Y,
     hipLaunchKernelGGL(k_qrg, dim3(f.items), dim3(kQrgThreads), 0, st, q);
   }
   (void)panel;
+  return hipGetLastError();
+}
+
+// One launch for every visit of columns col_hi .. col_lo where the shape fits
+// k_absorb_small: D = 2, d = 2, FP64 and the LDS of one workgroup (bond caps up
+// to 20).
+static size_t small_lds(int K) {
+  return 8 * (K <= 8    ? SmallShape<1, 1>::words(K)
+              : K <= 16 ? SmallShape<1, 4>::words(K)
+                        : SmallShape<2, 4>::words(K));
+}
+bool absorb_small_fits(const FitBatch &f) {
+  return f.D == 2 && f.d == 2 && f.prec == 64 && f.K <= 32 && f.N >= 3 &&
+         small_lds(f.K) + 4096 <= 160 * 1024;
+}
+hipError_t launch_absorb_small(const FitBatch &f, int col_hi, int col_lo, int n_fit,
+                               hipStream_t st) {
+  static std::once_flag once;
+  static hipError_t attr = hipSuccess;
+  std::call_once(once, [] {
+    for (const void *k : {(const void *)k_absorb_small<1, 1>, (const void *)k_absorb_small<1, 4>,
+                          (const void *)k_absorb_small<2, 4>}) {
+      const hipError_t e =
+          hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
+      if (e != hipSuccess) attr = e;
+    }
+  });
+  if (attr != hipSuccess) return attr;
+  Count t;
+  auto add = [&](const Count &c) {
+    t.flops += c.flops;
+    t.bytes += c.bytes;
+  };
+  if (timing_enabled())
+    for (int c = col_lo; c <= col_hi; ++c) {
+      const int N = f.N;
+      for (int j = 1; j < N - 1; ++j) {
+        add(count_inner(f, c, j, true, TC_T1 | TC_KET | TC_BRA | TC_ENV));
+        for (int k = 0; k < n_fit; ++k)
+          for (bool rl : {false, true})
+            add(count_inner(f, c, j, rl, TC_T1 | TC_KET | TC_BRA | TC_LOCAL | TC_ENV));
+      }
+      add(count_end(f, c, true, 1 | 4));
+      for (int k = 0; k < n_fit; ++k)
+        for (bool rl : {false, true}) add(count_end(f, c, rl, 1 | 2 | 4));
+      add(count_end(f, c, false, 1 | 2));
+    }
+  Span sp(KC_VISIT, st, t.flops, t.bytes);
+  SmallArgs g{f, col_lo, col_hi, n_fit};
+  const size_t lds = small_lds(f.K);
+  const auto k = f.K <= 8    ? k_absorb_small<1, 1>
+                 : f.K <= 16 ? k_absorb_small<1, 4>
+                             : k_absorb_small<2, 4>;
+  hipLaunchKernelGGL(k, dim3(f.items), dim3(256), lds, st, g);
   return hipGetLastError();
 }
 

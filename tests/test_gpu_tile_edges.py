@@ -70,3 +70,13 @@ def test_visit_edges(D, H, chi):
     columns, rows that leave a tile of yf or xb partly empty, and the split of
     the xb range over workgroups."""
     _compare(D, H, 2, chi)
+
+
+@pytest.mark.parametrize("H,W,chi", [
+    (1, 1, 1), (1, 3, 4), (2, 2, 8), (5, 3, 8), (4, 2, 9), (6, 2, 16), (6, 3, 17), (6, 2, 20),
+])
+def test_small_columns(H, W, chi):
+    """The column absorptions that run as one launch (D = 2, bond caps to 20):
+    the shortest column, panels for one wave (to 8) and for four, and the
+    change from one column tile to two."""
+    _compare(2, H, W, chi)
