@@ -149,3 +149,24 @@ def test_non_finite_input_stays_in_its_item():
     # the NaN column's value sorts last, so it shows in the discarded weight;
     # the infinite column's value comes first
     assert np.isnan(e2[0]) and S[2][0] == np.inf
+
+
+# Matrices at the edges of the register kernel's instances (one wave per eight
+# columns, row counts of 64 R) and the first ones beyond them, against LAPACK
+# with this file's tolerances.
+@pytest.mark.parametrize("m,n,k", [
+    (2, 2, 1), (64, 8, 8), (65, 9, 4), (128, 17, 17), (193, 64, 5), (320, 53, 53), (321, 53, 9),
+    (384, 46, 46), (385, 41, 20), (512, 34, 16), (513, 33, 33),
+])
+def test_register_kernel_edges(m, n, k):
+    A = dense_matrices(2, m, n, seed=m + n, kind="gauss")
+    U, S, V, e2, sw = _run(A, k)
+    for b in range(2):
+        Uo, So, Vo, eo = _oracle(A[b], k)
+        tol = 32 * m * EPS * So[0]
+        assert sw[b] > 0
+        assert np.abs(S[b] - So).max() <= tol and abs(e2[b] - eo) <= 2 * tol * So[0]
+        res = A[b] @ V[b] - U[b] * S[b]
+        assert np.abs(res).max() <= tol
+        assert np.abs(U[b].T @ U[b] - np.eye(k)).max() <= 32 * m * EPS
+        assert np.abs(V[b].T @ V[b] - np.eye(k)).max() <= 32 * m * EPS
