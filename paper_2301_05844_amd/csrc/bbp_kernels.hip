@@ -2684,18 +2684,13 @@ __device__ __forceinline__ double join_f64(int lo, int hi) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// Sum over the four 16-lane rows: row pairs (0,1), (2,3) through
-// permlane16_swap, then the two pair sums through permlane32_swap; the same
-// bits land in every row.
+// Sum over the four 16-lane rows: the 4x4x4 MFMA multiplies a matrix of ones
+// (row index: the lane row of the result) by x (k: the lane row), so the same
+// bits land in every row after one instruction (35 cycles) instead of two
+// rounds of permlane swaps (70 cycles, 14 instructions).  Needs all 64 lanes
+// active.
 __device__ __forceinline__ double sum_rows4(double x) {
-  long long b = __double_as_longlong(x);
-  auto lo = __builtin_amdgcn_permlane16_swap((int)b, (int)b, false, false);
-  auto hi = __builtin_amdgcn_permlane16_swap((int)(b >> 32), (int)(b >> 32), false, false);
-  x = join_f64(lo[0], hi[0]) + join_f64(lo[1], hi[1]);
-  b = __double_as_longlong(x);
-  lo = __builtin_amdgcn_permlane32_swap((int)b, (int)b, false, false);
-  hi = __builtin_amdgcn_permlane32_swap((int)(b >> 32), (int)(b >> 32), false, false);
-  return join_f64(lo[0], hi[0]) + join_f64(lo[1], hi[1]);
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, x, 0.0, 0, 0, 0);
 }
 
 __device__ __forceinline__ int cl_index(int i, int j) {  // accumulator slot of (i, j)
@@ -2707,6 +2702,48 @@ template <int SRC>
 __device__ __forceinline__ double row_bcast(double x) {
   return __longlong_as_double(
       __builtin_amdgcn_mov_dpp(__double_as_longlong(x), 0x150 + SRC, 0xf, 0xf, true));
+}
+
+// p[s] += x[s] bcast(x[s]) and x[s] += bcast(x[s]) c for the four registers of
+// a tile, bcast the value of lane SRC of the 16-lane row: FMAs that take it
+// as their DPP operand.  Broadcasts of their own (which the compiler does not
+// fold into the FMA) double a column step's FP64 instructions.  s_nop 1 covers
+// the two wait states between a VALU write of x and its DPP read.
+template <int SRC>
+__device__ __forceinline__ void dot_bcast(double (&p)[4], const v4d &x) {
+  asm volatile(
+      "s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %4, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %5, %5 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %6, %6 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %3, %7, %7 row_newbcast:%8 row_mask:0xf bank_mask:0xf"
+      : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3])
+      : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "n"(SRC));
+}
+// x[s] += y_s bcast(g), bcast the value of lanes Q + s of the 16-lane row
+template <int Q>
+__device__ __forceinline__ void fma_bcast4(double (&x)[4], double y0, double y1, double y2,
+                                           double y3, double g) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %8, %4 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %8, %5 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %8, %6 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %3, %8, %7 row_newbcast:%12 row_mask:0xf bank_mask:0xf"
+      : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3])
+      : "v"(y0), "v"(y1), "v"(y2), "v"(y3), "v"(g), "n"(Q), "n"(Q + 1), "n"(Q + 2), "n"(Q + 3));
+}
+template <int SRC>
+__device__ __forceinline__ void axpy_bcast(v4d &x, double c) {
+  double x0 = x[0], x1 = x[1], x2 = x[2], x3 = x[3];
+  asm volatile(
+      "s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %0, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %1, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %2, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %3, %3, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
+      : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3)
+      : "v"(c), "n"(SRC));
+  x = v4d{x0, x1, x2, x3};
 }
 
 // dlarfg's scalars from alpha and sigma^2 > 0: nrm = sqrt(alpha^2 + sigma^2),
@@ -2753,7 +2790,6 @@ struct QmShared {
   double wp[2][NW > 1 ? 16 : 1][NW + 2], wq[2][16];
   double G[16][16];   // G[k][c] = v_c^T v_k, c < k
   double T[16][17];   // dlarft's T
-  double tau[16];
 };
 
 // Sum of the waves' 16x16 accumulators into Ws (accumulator slots).
@@ -2791,12 +2827,14 @@ __device__ __forceinline__ void qm_reduce(const v4d &acc, double (*wred)[256], d
 // leftovers of 1e-16 would otherwise be normalised to full columns by the next
 // site's factorisation.
 //
-// Bound by the dependent chain of a step (one barrier, two sums over the row
-// groups, dlarfg).  After the barrier a lane reads the partials of NW / 4
-// waves and the row groups' sums meet in registers: reading all NW partials
-// of its own and of column k in every lane (18 reads per lane and wave) kept
-// the LDS port busy for 576 cycles of a step's 1400.  A panel of one wave (NW
-// = 1) needs neither LDS nor a barrier in a step.
+// Bound by the instructions of a step, about 100 of them beside the tiles'
+// own, which every wave issues for itself, and by their dependent chain (one
+// barrier, two sums over the row groups, dlarfg).  After the barrier a lane
+// reads the partials of NW / 4 waves and one MFMA adds the row groups' sums.
+// Broadcasts folded into the tiles' FMAs, rows of R taken out of the tile
+// instead of masked in each step, those sums on MFMA and T from registers took
+// a 16-column block of 512 rows from 34900 to 28900 cycles.  A panel of one
+// wave (NW = 1) needs neither LDS nor a barrier in a step.
 template <int NW, int RT>
 __device__ __forceinline__ void qm_factor(v4d (&a)[RT], int b, int nbb, QmShared<NW> &sh,
                                           double (*wred)[256], double *Ws,
@@ -2804,6 +2842,24 @@ __device__ __forceinline__ void qm_factor(v4d (&a)[RT], int b, int nbb, QmShared
   const int lane = tid & 63, wave = tid >> 6;
   const int lr = lane >> 4, lc = lane & 15, b0 = 16 * b;
   double my_scal = 0.0, my_beta = 0.0, my_tau = 0.0;  // of column b0 + lc
+  // The tiles may come from MFMAs, whose results the FMAs written as assembly
+  // must not read for 19 wait states.  (Register by register: a tile as one
+  // operand made the allocator keep a copy of each, 18 tiles then spilled.)
+#pragma unroll
+  for (int t = RT - 1; t >= 0; --t) {
+    double x[4] = {a[t][0], a[t][1], a[t][2], a[t][3]};
+    if (t > 0) asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
+    else asm volatile("s_nop 15\n\ts_nop 3" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
+    a[t] = v4d{x[0], x[1], x[2], x[3]};
+  }
+  // rows of R leave the tile as they are finished (zero instead, so that no
+  // step has to mask them) and come back at the end
+  double rsave[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    rsave[s] = a[0][s];
+    if (16 * wave < b0) a[0][s] = 0.0;
+  }
   static_for<0, 16>([&](auto KC) __attribute__((always_inline)) {
     constexpr int kc = decltype(KC)::value, pb = kc & 1;
     if (kc >= nbb) return;
@@ -2811,23 +2867,13 @@ __device__ __forceinline__ void qm_factor(v4d (&a)[RT], int b, int nbb, QmShared
     // step compares anew instead of keeping 64 lane masks in scalar registers
     int r0 = 16 * wave + lr - b0;
     asm volatile("" : "+v"(r0));
-    constexpr bool keep = RT <= 6;  // x held from the sums to the update
-    double x0[4], pp[4], xt[keep ? RT : 1][4];
+    const double rk = a[0][kc >> 2];  // in the lanes of row k: a_kc
+    const bool in_k = r0 == (kc & 3);
+    if (NW > 1 && in_k) sh.wq[pb][lc] = rk;
+    if (in_k && lc >= kc) a[0][kc >> 2] = 0.0;
+    double pp[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      x0[s] = row_bcast<kc>(a[0][s]);
-      if (r0 + 4 * s <= kc) x0[s] = 0.0;
-      pp[s] = x0[s] * a[0][s];
-    }
-    if (NW > 1 && r0 == (kc & 3)) sh.wq[pb][lc] = a[0][kc >> 2];  // the lanes of row k
-#pragma unroll
-    for (int t = 1; t < RT; ++t)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const double x = row_bcast<kc>(a[t][s]);
-        if constexpr (keep) xt[t][s] = x;
-        pp[s] = fma(x, a[t][s], pp[s]);
-      }
+    for (int t = 0; t < RT; ++t) dot_bcast<kc>(pp, a[t]);
     const double pdot = sum_rows4((pp[0] + pp[1]) + (pp[2] + pp[3]));
     double pc, qc;
     if constexpr (NW > 1) {
@@ -2840,7 +2886,7 @@ __device__ __forceinline__ void qm_factor(v4d (&a)[RT], int b, int nbb, QmShared
       pc = sum_rows4(part);
     } else {
       pc = pdot;
-      qc = sum_rows4(lr == (kc & 3) ? a[0][kc >> 2] : 0.0);
+      qc = sum_rows4(in_k ? rk : 0.0);
     }
     const Reflector h = make_reflector(row_bcast<kc>(qc), row_bcast<kc>(pc));
     const double w = fma(h.scal, pc, qc);
@@ -2853,33 +2899,22 @@ __device__ __forceinline__ void qm_factor(v4d (&a)[RT], int b, int nbb, QmShared
     // dlarf on the block's columns c > k: a_c -= tau v w_c, v = (1, scal x)
     const double wt = (lc > kc && lc < nbb) ? -(h.tau * w) : 0.0;
     const double cs = h.scal * wt;
+    if (in_k) rsave[kc >> 2] = qc + wt;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) a[0][s] = fma(x0[s], cs, a[0][s]);
-    a[0][kc >> 2] += r0 == (kc & 3) ? wt : 0.0;
-#pragma unroll
-    for (int t = 1; t < RT; ++t)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        double x;
-        if constexpr (keep) x = xt[t][s];
-        else x = row_bcast<kc>(a[t][s]);
-        a[t][s] = fma(x, cs, a[t][s]);
-      }
+    for (int t = 0; t < RT; ++t) axpy_bcast<kc>(a[t], cs);
   });
-  // reflectors scaled in place, beta on the diagonal
-  if (lc < nbb) {
-    const int pr = b0 + lc;
+  asm volatile("s_nop 1");  // before an MFMA reads what they wrote
+  // reflectors scaled in place, beta on the diagonal, R above it
+  {
+    const double f = lc < nbb && my_tau != 0.0 ? my_scal : 1.0;
+    const int d0 = 16 * wave + lr - b0 - lc;  // first row minus the column's diagonal
 #pragma unroll
-    for (int t = 0; t < RT; ++t)
+    for (int s = 0; s < 4; ++s) {
+      const double x = a[0][s] * (d0 + 4 * s > 0 ? f : 1.0);
+      a[0][s] = d0 + 4 * s < 0 ? rsave[s] : d0 + 4 * s == 0 && lc < nbb ? my_beta : x;
+    }
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int row = 16 * (wave + NW * t) + 4 * s + lr;
-        if (t > 0 || row > pr) {
-          if (my_tau != 0.0) a[t][s] *= my_scal;
-        } else if (row == pr) {
-          a[t][s] = my_beta;
-        }
-      }
+    for (int t = 1; t < RT; ++t) a[t] *= f;
   }
   if (__ballot(lc < nbb && my_tau == 0.0) != 0) {  // the same in every wave
     v4d acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
@@ -2902,26 +2937,41 @@ __device__ __forceinline__ void qm_factor(v4d (&a)[RT], int b, int nbb, QmShared
 #pragma unroll
       for (int s = 0; s < 4; ++s) sh.G[lc][4 * s + lr] = acc[0][s];
   }
-  // T as in dlarft (forward, columnwise), by the wave that holds G: lane
-  // (lr, lc) keeps T[lc][lr + 4u]; column i of T needs columns < i
+  // T as in dlarft (forward, columnwise), by the wave that holds G: lane lc
+  // keeps row lc, so that column i is a sum over the lane's own registers with
+  // row i of G as DPP broadcasts (4 partial sums by column mod 4).  With a
+  // row's columns spread over the lane rows, and so a cross-lane sum and an LDS
+  // read in the chain of every column, T took 4700 cycles, a seventh of a
+  // block's time.
   if (wave == 0) {
-    if (lr == 0) sh.tau[lc] = my_tau;
     wave_lds_order();
-    double tr[4] = {0.0, 0.0, 0.0, 0.0};
+    double tr[16], g[16];
+    static_for<0, 4>([&](auto UC) __attribute__((always_inline)) {
+      constexpr int u = 4 * decltype(UC)::value;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      if (i >= nbb) continue;
-      const double ti = sh.tau[i];
-      double x = 0.0;
+      for (int i = u; i < u + 4; ++i) tr[i] = g[i] = 0.0;
+      if (u >= nbb) return;
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (4 * u < i && lr + 4 * u < i) x += tr[u] * sh.G[i][lr + 4 * u];
-      x = sum_rows4(x);
-      const double t = lc < i ? -ti * x : (lc == i ? ti : 0.0);
-      if (lr == (i & 3)) tr[i >> 2] = t;
-    }
+      for (int i = u; i < u + 4; ++i) g[i] = sh.G[i][lc];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) sh.T[lc][lr + 4 * u] = tr[u];
+      for (int i = u; i < u + 4; ++i) g[i] = lc < i && i < nbb ? g[i] : 0.0;
+    });
+    tr[0] = lc == 0 ? my_tau : 0.0;
+    static_for<1, 16>([&](auto IC) __attribute__((always_inline)) {
+      constexpr int i = decltype(IC)::value;
+      if (i >= nbb) return;
+      const double ti = row_bcast<i>(my_tau);
+      double x[4] = {0.0, 0.0, 0.0, 0.0};
+      static_for<0, (i + 3) / 4>([&](auto QC) __attribute__((always_inline)) {
+        constexpr int q = 4 * decltype(QC)::value;  // columns >= i meet a zero tr
+        fma_bcast4<q>(x, tr[q], tr[q + 1], tr[q + 2], tr[q + 3], g[i]);
+      });
+      const double xs = (x[0] + x[1]) + (x[2] + x[3]);
+      tr[i] = lc < i ? -ti * xs : (lc == i ? ti : 0.0);
+    });
+    if (lr == 0)
+#pragma unroll
+      for (int k = 0; k < 16; ++k) sh.T[lc][k] = tr[k];
   }
 }
 
@@ -3079,38 +3129,70 @@ __device__ __forceinline__ void qm_panel(v4d (&a)[CT][RT], int n, QmBuf<NW, RT, 
   });
 }
 
+// Calls f(ct, t, s, byte offset) for every entry a lane holds, entries outside
+// the panel at byte offset `out`.  Without a gap between the runs of rows the
+// offsets are linear in the row and every entry costs four instructions; the
+// gap's division, decided per entry, made them fifteen, 5000 cycles of a 512 x
+// 32 panel's 92000.
+template <int NW, int RT, int CT, class F>
+__device__ __forceinline__ void qr_entries(const QrPanel &p, unsigned out, F &&f) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lr = lane >> 4, lc = lane & 15, r0 = 16 * wave + lr;
+  int lim[CT];  // row 16 NW t + 4 s + r0 of column tile ct is real below this
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) lim[ct] = 16 * ct + lc < p.n ? p.m - r0 : 0;
+  const unsigned col = (unsigned)__mul24(lc, p.cs);
+  if (p.ex == 0) {
+    const unsigned o0 = (col + (unsigned)__mul24(r0, p.rs)) * 8u;
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int c = 16 * NW * t + 4 * s;
+        const unsigned o = o0 + (unsigned)(c * p.rs) * 8u;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+          f(ct, t, s, c < lim[ct] ? o + (unsigned)(16 * ct * p.cs) * 8u : out);
+      }
+  } else {
+    const DivN d(p.n2);
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int c = 16 * NW * t + 4 * s, row = c + r0;
+        const unsigned o =
+            (col + (unsigned)(__mul24(row, p.rs) + __mul24(d.quot(row), p.ex))) * 8u;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+          f(ct, t, s, c < lim[ct] ? o + (unsigned)(16 * ct * p.cs) * 8u : out);
+      }
+  }
+}
+
 // One workgroup per panel of up to 16 NW RT rows and 16 CT columns.  Bound by
-// the chain of column steps.  Against the form that took V^T V by MFMA, formed
-// the block coefficients in a pass of their own through LDS and used 64-bit
-// panel offsets: one 512 x 32 panel 42.6 -> 34.8 us, 672 x 42 (four to
-// sixty-four of them) 120 -> 86 us, 135 x 15 14.7 -> 12.0 us (kernel trace).
+// the chain of column steps: one 512 x 32 panel 42.6 us at first, 34.8 with
+// V^T V from the steps' sums and 24-bit offsets, 32.2 now; 768 x 48 (four to
+// sixty-four of them) 120, 91, 71 us; 135 x 15 14.7, 12.0, 10.1 us (kernel
+// trace).
 template <int NW, int RT, int CT>
 __global__ __launch_bounds__(NW * 64) void k_qrm(QrArgs q) {
   const int it = blockIdx.x;
   if (q.flag && !q.flag[it]) return;
   const QrPanel pn = qr_panel(q, it);
-  const int K = q.K, m = pn.m, n = pn.n;
+  const int K = q.K, n = pn.n;
   double *base = q.Y.at(it);
   __shared__ QmBuf<NW, RT, CT> sm;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane >> 4, lc = lane & 15;
   auto rowof = [&](int t, int s) { return 16 * (wave + NW * t) + 4 * s + lr; };
-  const DivN dn2(pn.n2);
 
   // entries outside the panel load past the descriptor's end and read zero
   const unsigned ybytes = (unsigned)(K * q.P * K) * 8u;
   const __amdgpu_buffer_rsrc_t yrs = buf_rsrc(base, ybytes);
   v4d a[CT][RT];
-#pragma unroll
-  for (int t = 0; t < RT; ++t)
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int row = rowof(t, s);
-      const unsigned o = (unsigned)(pn.row_off(row, dn2) + __mul24(lc, pn.cs));
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct)
-        a[ct][t][s] = buf_ld(yrs, row < m && 16 * ct + lc < n ? (o + 16 * ct * pn.cs) * 8u : ybytes);
-    }
+  qr_entries<NW, RT, CT>(pn, ybytes, [&](int ct, int t, int s, unsigned o) __attribute__((
+      always_inline)) { a[ct][t][s] = buf_ld(yrs, o); });
 
   qm_panel<NW, RT, CT>(a, n, sm, [&]() __attribute__((always_inline)) {
     if (!q.want_r) return;
@@ -3132,18 +3214,12 @@ __global__ __launch_bounds__(NW * 64) void k_qrm(QrArgs q) {
   // kept in registers from the load; a masked entry's store is dropped at the
   // descriptor's end.
   QrPanel po = pn;
-  asm volatile("" : "+v"(po.m), "+v"(po.n), "+v"(po.rs), "+v"(po.cs), "+v"(po.ex));
-#pragma unroll
-  for (int t = 0; t < RT; ++t)
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int row = rowof(t, s);
-      const unsigned o = (unsigned)(po.row_off(row, dn2) + __mul24(lc, po.cs));
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct)
-        buf_st_t<double>(yrs, row < po.m && 16 * ct + lc < po.n ? (o + 16 * ct * po.cs) * 8u : ybytes,
-                         a[ct][t][s]);
-    }
+  for (int *v : {&po.m, &po.n, &po.rs, &po.cs, &po.ex}) {
+    *v = __builtin_amdgcn_readfirstlane(*v);
+    asm volatile("" : "+s"(*v));
+  }
+  qr_entries<NW, RT, CT>(po, ybytes, [&](int ct, int t, int s, unsigned o) __attribute__((
+      always_inline)) { buf_st_t<double>(yrs, o, a[ct][t][s]); });
 }
 
 // ---------------------------------------------------------------------------
@@ -3161,7 +3237,7 @@ __global__ __launch_bounds__(NW * 64) void k_qrm(QrArgs q) {
 //
 // Bound by the chain: 64 column steps of about 1 us (the VALU work of 2304
 // rows on one CU), then one block application per launch.  One 2304 x 64
-// panel takes 4 launches of 38 us and 43 us for Q, 196 us together; k_qrg, a
+// panel takes 4 launches of 32 us and 43 us for Q, 171 us together; k_qrg, a
 // 16-wave workgroup per panel that streams the trailing panel from L2 once
 // for the dots and once for the update of every column, takes 2739 us, bound
 // by one CU's L2 port.
@@ -4376,17 +4452,32 @@ bool qr_needs_scratch(const FitBatch &f) {
   return (size_t)f.K * f.P * f.K > (size_t)kQrLds;
 }
 
+template <int NW, int RT, int CT>
+void launch_qrm_as(int items, hipStream_t st, const QrArgs &q) {
+  hipLaunchKernelGGL((k_qrm<NW, RT, CT>), dim3(items), dim3(NW * 64), 0, st, q);
+}
+
 template <int RT>
 void launch_qrm_rt(int CT, int items, hipStream_t st, const QrArgs &q) {
   constexpr int NW = kQmWavesUsed;
-  if (CT == 1) hipLaunchKernelGGL((k_qrm<NW, RT, 1>), dim3(items), dim3(NW * 64), 0, st, q);
-  else if (CT == 2) hipLaunchKernelGGL((k_qrm<NW, RT, 2>), dim3(items), dim3(NW * 64), 0, st, q);
-  else hipLaunchKernelGGL((k_qrm<NW, RT, 3>), dim3(items), dim3(NW * 64), 0, st, q);
+  if (CT == 1) launch_qrm_as<NW, RT, 1>(items, st, q);
+  else if (CT == 2) launch_qrm_as<NW, RT, 2>(items, st, q);
+  else launch_qrm_as<NW, RT, 3>(items, st, q);
 }
 
 void launch_qrm(const FitBatch &f, hipStream_t st, const QrArgs &q) {
-  const int rt = (f.K * f.P + 16 * kQmWavesUsed - 1) / (16 * kQmWavesUsed);
-  const int CT = (f.K + 15) / 16;
+  const int m = f.K * f.P, CT = (f.K + 15) / 16;
+  // Up to 256 x 16 four waves, one per SIMD: what every wave issues for itself
+  // in a step is then issued once per SIMD (135 x 15: 10.1 us, with eight waves
+  // 11.4).  Larger panels share their tiles' work over eight (512 x 32: 85600
+  // cycles with four, 82200 with eight).
+  if (CT == 1 && m <= 256) {
+    if (m <= 64) launch_qrm_as<4, 1, 1>(f.items, st, q);
+    else if (m <= 128) launch_qrm_as<4, 2, 1>(f.items, st, q);
+    else launch_qrm_as<4, 4, 1>(f.items, st, q);
+    return;
+  }
+  const int rt = (m + 16 * kQmWavesUsed - 1) / (16 * kQmWavesUsed);
   if (rt <= 1) launch_qrm_rt<1>(CT, f.items, st, q);
   else if (rt <= 2) launch_qrm_rt<2>(CT, f.items, st, q);
   else if (rt <= 4) launch_qrm_rt<4>(CT, f.items, st, q);

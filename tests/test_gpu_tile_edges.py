@@ -80,3 +80,11 @@ def test_small_columns(H, W, chi):
     the shortest column, panels for one wave (to 8) and for four, and the
     change from one column tile to two."""
     _compare(2, H, W, chi)
+
+
+@pytest.mark.parametrize("D,chi", [
+    (3, 4), (3, 7), (3, 8), (3, 14), (3, 15),   # 36, 63 | 72, 126 | 135 rows of four waves
+    (5, 10), (5, 11),                           # 250 rows | 275 of eight
+])
+def test_single_column_tile_edges(D, chi):
+    _compare(D, 3, 2, chi)
