@@ -628,9 +628,9 @@ struct OpK5 {
 
 // ---- environment update after the QR, Lenv' = T3 . Y ----------------------
 // E[y'][wb][xb] = sum_{yf, l} Y[yf][l][y'] T3[yf][l][xb][wb]  (RL: Y[y'][l][yf]).
-// One workgroup per (item, 64 columns n = (xb, wb)) of 4 KS waves: wave w owns
-// the 16 columns w % 4 and all MT row tiles of y', over the k part w / 4 of
-// every chunk.  The T3 operand is read straight from global memory (16 lanes,
+// One workgroup per (item, 16 CG columns n = (xb, wb)) of CG KS waves: wave w
+// owns the 16 columns w % CG and all MT row tiles of y', over the k part w / CG
+// of every chunk.  The T3 operand is read straight from global memory (16 lanes,
 // 128 contiguous bytes); Y is staged in LDS in chunks of 32 KS k = (yf, l).
 // The next chunk of both is fetched into registers while the current one is
 // multiplied; one barrier per chunk.  The KS partial sums of a column tile are
@@ -647,22 +647,30 @@ struct EnvArgs {
   int W, c, j, N;
 };
 
-// k parts per workgroup: two up to 32 rows (MT <= 2); from MT = 3 one, which
-// leaves the registers for T3 two chunks ahead at MT = 3
-template <int MT> struct EnvShape {
-  static constexpr int KS = MT <= 2 ? 2 : 1;
-  static constexpr int kThreads = 256 * KS;
-  static constexpr int kWaves = KS == 2 ? 4 : 2;  // waves per SIMD the registers allow
+// CG column groups of 16 and KS k parts per workgroup, a wave each.  Batches
+// that fill the CUs: four groups and, up to 32 rows (MT <= 2), two k parts;
+// from MT = 3 one, which leaves the registers for T3 two chunks ahead at MT =
+// 3.  Small batches (FILL = false), where each chunk waits for a round trip to
+// memory (2 us: T3 and Y come from other XCDs): half the columns, and two (MT
+// = 2, as LDS allows) or four times the k range a chunk.
+// Eight items of 32 rows 17.8 -> 13.4 us, four of 48 40.4 -> 26.7, one of 64
+// rows and 2304 columns 144 -> 88; of 16 rows it was slower (6.0 and 6.4 us).
+template <int MT, bool FILL = true> struct EnvShape {
+  static constexpr int CG = FILL ? 4 : 2;
+  static constexpr int KS = FILL ? (MT <= 2 ? 2 : 1) : 4;
+  static constexpr int kThreads = 64 * CG * KS;
+  static constexpr int kWaves = MT <= 2 && FILL ? 4 : 2;  // waves per SIMD the registers allow
 };
 
 // B16 (T = float): BF16 MFMA, the eight T3 rows a lane holds per chunk
 // feeding two 16-deep steps (rows 4i + lq, i = 0-3 and 4-7).
-template <int MT, class T, bool B16 = false>
-__global__ __launch_bounds__(EnvShape<MT>::kThreads)
-__attribute__((amdgpu_waves_per_eu(EnvShape<MT>::kWaves))) void k_env(EnvArgs e) {
+template <int MT, class T, bool B16 = false, bool FILL = true>
+__global__ __launch_bounds__((EnvShape<MT, FILL>::kThreads))
+__attribute__((amdgpu_waves_per_eu((EnvShape<MT, FILL>::kWaves)))) void k_env(EnvArgs e) {
+  typedef EnvShape<MT, FILL> S;
   typedef Mma<T> M;
   typedef typename M::acc Acc;
-  constexpr int KS = EnvShape<MT>::KS, NT = EnvShape<MT>::kThreads;
+  constexpr int KS = S::KS, CG = S::CG, NT = S::kThreads;
   constexpr int MW = MT * 16, AS = M::pad_b(MW), CH = 32 * KS;
   constexpr int NA = CH * MW / NT;  // A elements staged per thread
   __shared__ T As[2][CH][AS];
@@ -670,8 +678,8 @@ __attribute__((amdgpu_waves_per_eu(EnvShape<MT>::kWaves))) void k_env(EnvArgs e)
   int tile, it;
   xcd_tile_item(&tile, &it);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int lr = lane & 15, lq = lane >> 4, cg = wave & 3, h = wave >> 2;
-  const int n = tile * 64 + cg * 16 + lr;
+  const int lr = lane & 15, lq = lane >> 4, cg = wave % CG, h = wave / CG;
+  const int n = (tile * CG + cg) * 16 + lr;
   // k = (yf, l) runs to the true front bond of Y, columns n = (xb, wb) to the
   // true X bond; past them every product is zero (Y padding) or T3 was not
   // written, so they are skipped (or masked) without changing any sum.  E is
@@ -682,14 +690,13 @@ __attribute__((amdgpu_waves_per_eu(EnvShape<MT>::kWaves))) void k_env(EnvArgs e)
     Kd = ex.yf * P;
     Nt = ex.xb * P;
   }
-  if (tile * 64 >= Nt) {  // every column of the tile is padding
-    if (tid < 64 * 4) {
-      auto *Ez = gmem(e.E.at(it));
-      const int nz = tile * 64 + tid % 64;
-      if (nz < N) {
-        const int xb = nz / P, wb = nz - xb * P;
-        for (int m = tid / 64; m < K; m += 4) Ez[((size_t)m * P + wb) * K + xb] = 0.0;
-      }
+  if (tile * 16 * CG >= Nt) {  // every column of the tile is padding
+    auto *Ez = gmem(e.E.at(it));
+    const int nz = tile * 16 * CG + tid % (16 * CG);
+    if (nz < N) {
+      const int xb = nz / P, wb = nz - xb * P;
+      for (int m = tid / (16 * CG); m < K; m += NT / (16 * CG))
+        Ez[((size_t)m * P + wb) * K + xb] = 0.0;
     }
     return;
   }
@@ -809,13 +816,13 @@ __attribute__((amdgpu_waves_per_eu(EnvShape<MT>::kWaves))) void k_env(EnvArgs e)
   for (int mt = 0; mt < MT; ++mt) c[mt] = NC == 1 ? acc[mt][0] : acc[mt][0] + acc[mt][NC - 1];
   if (KS > 1) {  // k parts 1.. hand their sums to part 0 through LDS
     T *red = &As[0][0][0];
-    static_assert((KS - 1) * 4 * MT * 4 * 64 <= 2 * CH * AS, "reduction fits");
+    static_assert((KS - 1) * CG * MT * 4 * 64 <= 2 * CH * AS, "reduction fits");
     if (h > 0) {
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          red[((((h - 1) * 4 + cg) * MT + mt) * 4 + r) * 64 + lane] = c[mt][r];
+          red[((((h - 1) * CG + cg) * MT + mt) * 4 + r) * 64 + lane] = c[mt][r];
     }
     __syncthreads();
     if (h > 0) return;
@@ -825,7 +832,7 @@ __attribute__((amdgpu_waves_per_eu(EnvShape<MT>::kWaves))) void k_env(EnvArgs e)
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          c[mt][r] += red[((((hh - 1) * 4 + cg) * MT + mt) * 4 + r) * 64 + lane];
+          c[mt][r] += red[((((hh - 1) * CG + cg) * MT + mt) * 4 + r) * 64 + lane];
   }
   if (n >= N) return;
   const int xb = n / P, wb = n - xb * P;
@@ -2279,12 +2286,12 @@ __global__ __launch_bounds__(kThreads) void k_sum_parts(Ptr Y, const double *par
   const int it = blockIdx.y;
   const auto *p = gmem(part) + (size_t)it * part_stride;
   auto *y = gmem(Y.at(it));
-  for (size_t i = blockIdx.x * (size_t)kThreads + threadIdx.x; i < n;
-       i += (size_t)gridDim.x * kThreads) {
-    double t = p[i];
-    for (int k = 1; k < nsplit; ++k) t += p[(size_t)k * n + i];
-    y[i] = t;
-  }
+  const size_t i = blockIdx.x * (size_t)kThreads + threadIdx.x;
+  if (i >= n) return;
+  double t = p[i];
+#pragma unroll 4
+  for (int k = 1; k < nsplit; ++k) t += p[(size_t)k * n + i];
+  y[i] = t;
 }
 
 // ---------------------------------------------------------------------------
@@ -4421,7 +4428,7 @@ static hipError_t launch_fused(const FitBatch &f, int c, int j, bool rl, Ptr X,
     hipLaunchKernelGGL(vp.k, dim3((f.K + vp.TY - 1) / vp.TY * g.nsplit, f.items),
                        dim3(vp.threads), vp.lds, st, g);
     if (do_local && g.nsplit > 1)
-      hipLaunchKernelGGL(k_sum_parts, dim3(64, f.items), dim3(kThreads), 0, st, Y,
+      hipLaunchKernelGGL(k_sum_parts, dim3((f.K * f.P * f.K + kThreads - 1) / kThreads, f.items), dim3(kThreads), 0, st, Y,
                          (const double *)f.t1, t1_stride(f), g.nsplit, (size_t)f.K * f.P * f.K);
   } else {
     const VisitKernel kf = b16   ? visit_kernel<float, true>(f.D)
@@ -4601,6 +4608,16 @@ hipError_t launch_inner_env(const FitBatch &f, int c, int j, bool rl, Ptr Y,
       else if (mt <= 2) hipLaunchKernelGGL((k_env<2, float>), grid, dim3(EnvShape<2>::kThreads), 0, st, e);
       else if (mt <= 3) hipLaunchKernelGGL((k_env<3, float>), grid, dim3(EnvShape<3>::kThreads), 0, st, e);
       else hipLaunchKernelGGL((k_env<4, float>), grid, dim3(EnvShape<4>::kThreads), 0, st, e);
+      return hipGetLastError();
+    }
+    // Fewer than 256 workgroups leave CUs idle and every chunk's round trip
+    // exposed: the shape for small batches, measured at EnvShape.
+    const long sel = f.tile_items > 0 ? f.tile_items : f.items;
+    if (mt > 1 && sel * grid.x < 256) {
+      const dim3 half((f.K * f.P + 31) / 32, f.items);
+      if (mt <= 2) hipLaunchKernelGGL((k_env<2, double, false, false>), half, dim3(EnvShape<2, false>::kThreads), 0, st, e);
+      else if (mt <= 3) hipLaunchKernelGGL((k_env<3, double, false, false>), half, dim3(EnvShape<3, false>::kThreads), 0, st, e);
+      else hipLaunchKernelGGL((k_env<4, double, false, false>), half, dim3(EnvShape<4, false>::kThreads), 0, st, e);
       return hipGetLastError();
     }
     if (mt <= 1) hipLaunchKernelGGL((k_env<1, double>), grid, dim3(EnvShape<1>::kThreads), 0, st, e);
