@@ -653,7 +653,7 @@ struct EnvArgs {
 // 3.  Small batches (FILL = false), where each chunk waits for a round trip to
 // memory (2 us: T3 and Y come from other XCDs): half the columns, and two (MT
 // = 2, as LDS allows) or four times the k range a chunk.
-// Eight items of 32 rows 17.8 -> 13.4 us, four of 48 40.4 -> 26.7, one of 64
+// One item of 32 rows 17.8 -> 13.4 us, four of 48 40.4 -> 26.7, one of 64
 // rows and 2304 columns 144 -> 88; of 16 rows it was slower (6.0 and 6.4 us).
 template <int MT, bool FILL = true> struct EnvShape {
   static constexpr int CG = FILL ? 4 : 2;
