@@ -4159,16 +4159,18 @@ static VisitKernel visit4_kernel(int TY, int TX) {
 static int visit4p_ne(int K) { return std::max(2, ceil16(K) / 16); }
 
 // Pair-per-wave visit (K <= 64): 2 x 2 pairs, 4 x 1 at NE = 3.  A small
-// batch at NE <= 2, whose 2 x 2 grid would not give every CU a workgroup,
-// takes 1 x 4 pairs: twice the workgroups, each walking a quarter of the
-// columns xb.
+// batch at NE <= 3, whose grid would not give every CU a workgroup, takes 1 x
+// 4 pairs: two or four times the workgroups, each walking a quarter of the
+// columns xb (4 and 8 items at K = 42, 44 and 88 workgroups of 4 x 1 pairs: 83
+// -> 39 us a launch; 24 items fill the CUs with 264).
 template <class T>
 static bool visit4p_tiles(const FitBatch &f, int *TY, int *TX, size_t *bytes) {
   if (f.D != 4 || f.d != 2 || f.K > 64) return false;
   const int ne = visit4p_ne(f.K);
   const long sel = f.tile_items > 0 ? f.tile_items : f.items;
-  const bool small = ne <= 2 && sel * ((f.K + 1) / 2) < 256;
-  const int ty = ne == 3 ? 4 : small ? 1 : 2, tx = ne == 3 ? 1 : small ? 4 : 2;
+  const bool small = (ne <= 2 && sel * ((f.K + 1) / 2) < 256) ||
+                     (ne == 3 && sizeof(T) == 8 && sel * ((f.K + 3) / 4) < 128);
+  const int ty = small ? 1 : ne == 3 ? 4 : 2, tx = small ? 4 : ne == 3 ? 1 : 2;
   const size_t n = visit4p_lds<T>(f.K, ty, tx) * sizeof(T);
   if (n > 150 * 1024) return false;
   *TY = ty;
@@ -4181,6 +4183,8 @@ static bool visit4p_tiles(const FitBatch &f, int *TY, int *TX, size_t *bytes) {
 template <class T>
 static VisitKernel visit4p_kernel(int NE, int TY) {
   if (NE <= 2) return TY == 1 ? k_visit4p<1, 4, T, 2> : k_visit4p<2, 2, T, 2>;
+  if constexpr (sizeof(T) == 8)
+    if (NE == 3 && TY == 1) return k_visit4p<1, 4, T, 3>;
   if (NE == 3) return k_visit4p<4, 1, T, 3>;
   return k_visit4p<2, 2, T, 4>;
 }

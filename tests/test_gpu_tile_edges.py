@@ -88,3 +88,10 @@ def test_small_columns(H, W, chi):
 ])
 def test_single_column_tile_edges(D, chi):
     _compare(D, 3, 2, chi)
+
+
+# one item at caps 33 to 48: the D = 4 visit's 1 x 4 pairs, back bonds in
+# whole and ragged steps of four
+@pytest.mark.parametrize("chi", [33, 36, 42, 48])
+def test_small_batch_visit_at_three_column_tiles(chi):
+    _compare(4, 4, 2, chi)
