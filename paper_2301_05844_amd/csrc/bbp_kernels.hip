@@ -1971,6 +1971,7 @@ struct VisitPArgs {
   int nsplit;        // xb ranges, one per workgroup of a yf tile
   double *part;      // nsplit > 1: partial Yt, [item][split][K P K]
   size_t part_stride;
+  const FitDims *dims;  // true bonds that the split is cut by (null: the bond cap)
 };
 
 template <int D, int TY, int TX, int NE>
@@ -2000,9 +2001,16 @@ void k_visitp(VisitPArgs g) {
     nxf = ex.xf;
     nxb = ex.xb;
   }
-  // this workgroup's xb range: nsplit contiguous ranges of whole steps
-  const int steps = (nxb + TX - 1) / TX;
-  const int xlo = steps * sp / g.nsplit * TX, xhi = min(nxb, steps * (sp + 1) / g.nsplit * TX);
+  // this workgroup's xb range: nsplit contiguous ranges of whole steps, cut by
+  // the true bond also where the padding is run (the last one takes it then),
+  // so that the partial sums hold the same terms either way
+  int steps = (nxb + TX - 1) / TX;
+  if (g.dims) {
+    const SiteExt ex = site_ext(g.dims[(size_t)it * v.W + v.c], v.j, v.N, rl);
+    steps = (ex.xb + TX - 1) / TX;
+  }
+  const int xlo = steps * sp / g.nsplit * TX;
+  const int xhi = sp == g.nsplit - 1 ? nxb : min(nxb, steps * (sp + 1) / g.nsplit * TX);
   double *Yout = g.nsplit > 1
                      ? g.part + (size_t)it * g.part_stride + (size_t)sp * K * P * K
                      : v.Y.at(it);
@@ -4428,7 +4436,7 @@ static hipError_t launch_fused(const FitBatch &f, int c, int j, bool rl, Ptr X,
                        dim3((f.K + TY4 - 1) / TY4, f.items), dim3(kVisitThreads), lds4, st, v);
   } else if (const VisitPChoice vp = b16 || f32 ? VisitPChoice{} : visitp_tiles(f); vp.k) {
     v.dims = f.bounded && f.hdims ? f.dims : nullptr;
-    VisitPArgs g{v, vp.nsplit, f.t1, t1_stride(f)};
+    VisitPArgs g{v, vp.nsplit, f.t1, t1_stride(f), f.hdims ? f.dims : nullptr};
     hipLaunchKernelGGL(vp.k, dim3((f.K + vp.TY - 1) / vp.TY * g.nsplit, f.items),
                        dim3(vp.threads), vp.lds, st, g);
     if (do_local && g.nsplit > 1)

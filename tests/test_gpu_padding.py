@@ -65,6 +65,31 @@ def test_skip_padding_bitwise_equal(case):
     assert np.array_equal(a[3], b[3])
 
 
+# The visits of the other bond dimensions, with true bonds (D^2 and less at the
+# two or three sites of a message) below the cap.  From D = 5 on, caps above 32
+# in a batch this small split the sum over xb among workgroups.
+OTHER_D = [
+    dict(Lx=6, Ly=6, bx=3, by=3, D=2, chi=24, chi_env=24),
+    dict(Lx=6, Ly=6, bx=3, by=3, D=3, chi=14, chi_env=14),
+    dict(Lx=6, Ly=6, bx=3, by=3, D=5, chi=28, chi_env=28),
+    dict(Lx=6, Ly=6, bx=3, by=3, D=5, chi=36, chi_env=36),
+    dict(Lx=4, Ly=4, bx=2, by=2, D=6, chi=50, chi_env=50),
+]
+
+
+@pytest.mark.parametrize("case", range(len(OTHER_D)))
+def test_skip_padding_bitwise_other_bond_dimensions(case):
+    kw = OTHER_D[case]
+    A = peps_finite(kw["Lx"], kw["Ly"], kw["D"], seed=31 + case)
+    print(f"case {kw}", flush=True)
+    a = _solve(0, A, 2, **kw)
+    b = _solve(1, A, 2, **kw)
+    assert np.array_equal(a[0], b[0])
+    for ma, mb in zip(a[1], b[1]):
+        assert np.array_equal(ma, mb)
+    assert np.array_equal(a[2], b[2]) and np.array_equal(a[3], b[3])
+
+
 @pytest.mark.parametrize("precision,graphs", [(32, 1), (64, 0)])
 def test_skip_padding_bitwise_fp32_and_eager(precision, graphs):
     kw = dict(Lx=8, Ly=12, bx=4, by=4, D=4, chi=32, chi_env=42)
