@@ -484,21 +484,52 @@ __global__ __launch_bounds__(64 * MAXW) void k_svd_reg(SvdArgs g) {
   }
 }
 
-// The register kernel's instance for m rows: R the row chunks of 64 it holds
-// (at least ceil(m / 64)), MAXW the waves the widest matrix of that height
-// needs under BBP_SVD_MAX_WORDS.  Beyond 512 rows few columns fit, so one to
-// four waves do what k_svd_jacobi's sixteen share: 256 matrices of 576 x 31
-// took 938 us in registers against 858, of 1024 x 19 794 against 485.
+// The register kernel's instance for up to `rows` rows: R the row chunks of 64
+// it holds, MAXW the waves the widest matrix of that height needs under
+// BBP_SVD_MAX_WORDS; and the columns from which it is the faster one (the two
+// give the same bits).  Beyond 512 rows few columns fit, so one to four waves
+// do what k_svd_jacobi's sixteen share: 256 matrices of 576 x 31 took 938 us in
+// registers against 858, of 1024 x 19 794 against 485.  The same holds for few
+// columns below that while a CU has one matrix (`one`, batches up to 256) or
+// two, all that k_svd_jacobi's waves leave room for (`two`, up to 512; matrices
+// of one wave, 8 columns, are the faster in registers there, `narrow`).  In
+// LDS and in registers, us: one 512 x 9 matrix 92 and 137, one 512 x 24 412 and
+// 436, 512 x 28 553 and 527; one 256 x 9 101 and 115, 256 x 20 292 and 247; 384
+// of 256 x 9 126 and 163, of 256 x 12 216 and 208, of 64 x 8 83 and 73.  In
+// larger batches registers win (2048 of 256 x 9 422 and 323) but for the first
+// columns of a third wave at 385 to 448 rows, where a chunk is empty, and at 512
+// (`many`; 2048 of 512 x 17 1340 and 1610).  At 512 rows k_svd_jacobi's loops
+// over rows are whole steps of eight, at 449 to 511 one by one (480 x 14 6 %
+// slower than in registers where 512 x 14 is 24 % faster).
 using SvdKernel = void (*)(SvdArgs);
 struct SvdChoice {
   SvdKernel k;
-  int R, maxw;
+  int rows, R, maxw;
+  int one, two, many;
+  bool narrow;
 };
 const SvdChoice kSvdReg[] = {
-    {k_svd_reg<1, 8>, 1, 8},   {k_svd_reg<2, 8>, 2, 8},   {k_svd_reg<3, 8>, 3, 8},
-    {k_svd_reg<4, 8>, 4, 8},   {k_svd_reg<5, 8>, 5, 8},   {k_svd_reg<6, 7>, 6, 7},
-    {k_svd_reg<8, 6>, 8, 6},
+    {k_svd_reg<1, 8>, 64, 1, 8, 10, 10, 0, true},
+    {k_svd_reg<2, 8>, 128, 2, 8, 10, 10, 0, true},
+    {k_svd_reg<3, 8>, 192, 3, 8, 11, 12, 0, true},
+    {k_svd_reg<4, 8>, 256, 4, 8, 11, 12, 0, true},
+    {k_svd_reg<5, 8>, 320, 5, 8, 18, 12, 0, true},
+    {k_svd_reg<6, 7>, 384, 6, 7, 18, 12, 0, true},
+    {k_svd_reg<8, 6>, 448, 8, 6, 18, 18, 18, false},
+    {k_svd_reg<8, 6>, 511, 8, 6, 10, 10, 0, true},
+    {k_svd_reg<8, 6>, 512, 8, 6, 26, 20, 20, false},
 };
+// The instance that takes the batch, or null: k_svd_jacobi.
+const SvdChoice *svd_in_registers(int batch, int m, int n, int waves) {
+  for (const SvdChoice &c : kSvdReg) {
+    if (m > c.rows) continue;
+    const bool ok = batch <= 256   ? n >= c.one
+                    : batch <= 512 ? n >= c.two || (c.narrow && n <= 2 * kSvdSlots)
+                                   : n <= 4 * kSvdSlots || n >= c.many;
+    return ok && waves <= c.maxw ? &c : nullptr;
+  }
+  return nullptr;
+}
 
 }  // namespace
 }  // namespace bbp
@@ -539,12 +570,10 @@ extern "C" bbp_status bbp_svd_jacobi(int32_t batch, int32_t m, int32_t n, int32_
   g.k = k;
   g.max_sweeps = max_sweeps;
   g.tol = tol > 0.0 ? tol : std::sqrt((double)m) * DBL_EPSILON;
-  // in registers where an instance takes the shape, else in LDS
   const int waves = ((n + 1) / 2 + kSvdSlots - 1) / kSvdSlots;
-  for (const SvdChoice &c : kSvdReg) {
-    if (m > 64 * c.R || waves > c.maxw) continue;
-    const size_t xch = waves > 1 ? (size_t)2 * waves * 2 * (c.R + 1) * 64 * sizeof(double) : 0;
-    hipLaunchKernelGGL(c.k, dim3(batch), dim3(64 * waves), xch, (hipStream_t)hip_stream, g);
+  if (const SvdChoice *c = svd_in_registers(batch, m, n, waves)) {
+    const size_t xch = waves > 1 ? (size_t)2 * waves * 2 * (c->R + 1) * 64 * sizeof(double) : 0;
+    hipLaunchKernelGGL(c->k, dim3(batch), dim3(64 * waves), xch, (hipStream_t)hip_stream, g);
     return hipGetLastError() == hipSuccess ? BBP_OK : BBP_EDEVICE;
   }
   const size_t lds = ((size_t)m * n + (size_t)n * n) * sizeof(double);

@@ -170,3 +170,56 @@ def test_register_kernel_edges(m, n, k):
         assert np.abs(res).max() <= tol
         assert np.abs(U[b].T @ U[b] - np.eye(k)).max() <= 32 * m * EPS
         assert np.abs(V[b].T @ V[b] - np.eye(k)).max() <= 32 * m * EPS
+
+
+# Both kernels give the same bits, so an item's result depends neither on the
+# batch that chooses between them nor on rows of zeros that lead past the
+# register kernel's height.
+
+
+@pytest.mark.parametrize("m,n", [
+    (2, 2), (64, 8), (65, 9), (192, 3), (200, 13), (320, 17), (448, 8), (511, 5),
+    (512, 9), (512, 16), (512, 25),
+])
+def test_bits_do_not_depend_on_the_batch_size(m, n):
+    """2 matrices, and the same in batches of 300 and 520 (two and three a CU)."""
+    A = dense_matrices(2, m, n, seed=m * n, kind="gauss")
+    one = _run(A, n)
+    assert np.all(one[4] > 0)
+    for batch in (300, 520):
+        many = _run(np.tile(A, (batch // 2, 1, 1)), n)
+        for x, y in zip(one, many):
+            assert np.array_equal(x, y[:2]) and np.array_equal(x, y[-2:])
+
+
+@pytest.mark.parametrize("m,n", [
+    (33, 10), (64, 16), (129, 25), (256, 36), (300, 19), (385, 31), (480, 11), (511, 24), (512, 36),
+])
+def test_bits_do_not_depend_on_zero_rows(m, n):
+    """Rows of zeros add exact zeros to every sum; past 512 rows the matrix stays
+    in LDS.  One tolerance for both (the default depends on m)."""
+    bbp, torch = _bbp()
+    A = dense_matrices(3, m, n, seed=m + 7 * n, kind="gauss")
+    out = []
+    for rows in (m, 513):
+        B = np.zeros((3, rows, n))
+        B[:, :m] = A
+        out.append([x.cpu().numpy() for x in
+                    bbp.svd_jacobi(torch.from_numpy(B).cuda(), n, tol=1e-14)])
+    (U, S, V, e2, sw), (Uz, Sz, Vz, ez, swz) = out
+    assert np.array_equal(S, Sz) and np.array_equal(V, Vz) and np.array_equal(e2, ez)
+    assert np.array_equal(sw, swz) and np.array_equal(U, Uz[:, :m]) and not Uz[:, m:].any()
+
+
+@pytest.mark.parametrize("m,n,k", [(2, 2, 1), (64, 8, 8), (65, 9, 4), (193, 1, 1), (448, 16, 5)])
+def test_register_kernel_of_few_columns(m, n, k):
+    """Few columns run in registers in large batches only."""
+    A = np.tile(dense_matrices(2, m, n, seed=m + n, kind="gauss"), (260, 1, 1))
+    U, S, V, e2, sw = _run(A, k)
+    for b in (0, 1, 518, 519):
+        Uo, So, Vo, eo = _oracle(A[b], k)
+        tol = 32 * m * EPS * So[0]
+        assert sw[b] > 0
+        assert np.abs(S[b] - So).max() <= tol and abs(e2[b] - eo) <= 2 * tol * So[0]
+        assert np.abs(A[b] @ V[b] - U[b] * S[b]).max() <= tol
+        assert np.abs(U[b].T @ U[b] - np.eye(k)).max() <= 32 * m * EPS
