@@ -340,7 +340,8 @@ bbp_status bbp_stats(bbp_ctx *c, int32_t *n_messages, double *sweep_flops);
  * the bond cap chi_env.  Synchronises the recorded events.  Classes:
  * fit_visit (the fused contractions of one fit visit on MFMA; for small
  * shapes, D=2 and bond caps to 20 in FP64, a whole column absorption with its
- * environments, corners and QRs in one launch), fit_T1,
+ * environments, corners and QRs in one launch: the operations of all of them,
+ * and the bytes that this launch loads and stores), fit_T1,
  * fit_ket, fit_bra, fit_local (the same contractions as separate kernels,
  * used when the fused tiles do not fit in LDS), fit_env (environment
  * recursion of App. A), fit_end (end-site contractions), qr (Householder

@@ -4723,6 +4723,69 @@ bool absorb_small_fits(const FitBatch &f) {
   return f.D == 2 && f.d == 2 && f.prec == 64 && f.K <= 32 && f.N >= 3 &&
          small_lds(f.K) + 4096 <= 160 * 1024;
 }
+// Counts of column c in k_absorb_small, true and at the bond cap: the
+// contractions and QRs of every visit, and the bytes that the kernel itself
+// loads and stores (T3, an end visit's G and the environment handed to the next
+// visit stay in LDS).
+static void count_small(const FitBatch &f, int c, int n_fit, Count *t, Count *pad) {
+  if (!timing_enabled()) return;
+  const int N = f.N;
+  const double P = f.P, site = 2.0 * f.d * P * P;
+  auto count = [&](const FitDims *d, const FitDims *next, bool rnd) {
+    const double K = f.K;
+    Count s;
+    auto qr = [&](double m, double n) { s.flops += 4.0 * m * n * n - 4.0 * n * n * n / 3.0; };
+    auto visit = [&](int j, bool rl, bool local, bool env) {
+      double yf = K, yb = K, xf = K, xb = K, m = 0.0, b = 0.0;
+      if (d) {
+        const SiteExt e = site_ext(*d, j, N, rl);
+        yf = e.yf, yb = e.yb, xf = e.xf, xb = e.xb;
+      }
+      const bool end = j == 0 || j == N - 1;
+      if (end) {
+        const double a = d ? d->p[j] : K, ap = d ? (c == f.W - 1 ? 1 : next->p[j]) : K;
+        m += a * P * ap * xb + (local ? a * P * xb * yb : 0.0) +
+             (env ? yb * a * P * xb : 0.0);
+        b += a * P * ap + ap * xb + a * yb;  // message site, X, Y
+        if (local && env) qr(d ? a : K * P, yb);
+      } else {
+        m += yf * P * xf * P * xb + 2.0 * yf * xb * f.d * P * P * P +
+             (local ? 2.0 : 1.0) * yf * P * xb * P * yb;
+        b += xf * P * xb + site + yf * P * yb;  // X, ket and bra, Y
+        if (local) {
+          b += yb * P * xb;  // G
+          qr(yf * P, yb);
+        }
+      }
+      const int jn = rl ? j - 1 : j + 1;
+      if (env && jn > 0 && jn < N - 1) b += yb * P * xb;  // kept for the sweep back
+      s.flops += 2.0 * m;
+      s.bytes += 8.0 * b;
+    };
+    for (int j = N - 1; j >= 1; --j) visit(j, true, false, true);
+    for (int k = 0; k < n_fit; ++k) {
+      for (int j = 0; j < N - 1; ++j) visit(j, false, true, true);
+      for (int j = N - 1; j >= 1; --j) visit(j, true, true, true);
+    }
+    visit(0, false, true, false);
+    if (rnd)  // the start: each site made, factorised and stored
+      for (int j = N - 1; j >= 1; --j) {
+        const double m = d ? (double)d->p[j] * d->br[j] : K * P, n = d ? d->bl[j] : K;
+        qr(m, n);
+        s.bytes += 8.0 * m * n;
+      }
+    return s;
+  };
+  const Count cap = count(nullptr, nullptr, false), cap_rnd = count(nullptr, nullptr, true);
+  for (int i = 0; i < f.items; ++i) {
+    const FitDims *d = f.hdims ? f.hdims + (size_t)i * f.W + c : nullptr;
+    const Count &y = d && d->rnd ? cap_rnd : cap, x = d ? count(d, d + 1, d->rnd) : y;
+    t->flops += x.flops;
+    t->bytes += x.bytes;
+    pad->flops += y.flops;
+    pad->bytes += y.bytes;
+  }
+}
 hipError_t launch_absorb_small(const FitBatch &f, int col_hi, int col_lo, int n_fit,
                                hipStream_t st) {
   static std::once_flag once;
@@ -4736,26 +4799,9 @@ hipError_t launch_absorb_small(const FitBatch &f, int col_hi, int col_lo, int n_
     }
   });
   if (attr != hipSuccess) return attr;
-  Count t;
-  auto add = [&](const Count &c) {
-    t.flops += c.flops;
-    t.bytes += c.bytes;
-  };
-  if (timing_enabled())
-    for (int c = col_lo; c <= col_hi; ++c) {
-      const int N = f.N;
-      for (int j = 1; j < N - 1; ++j) {
-        add(count_inner(f, c, j, true, TC_T1 | TC_KET | TC_BRA | TC_ENV));
-        for (int k = 0; k < n_fit; ++k)
-          for (bool rl : {false, true})
-            add(count_inner(f, c, j, rl, TC_T1 | TC_KET | TC_BRA | TC_LOCAL | TC_ENV));
-      }
-      add(count_end(f, c, true, 1 | 4));
-      for (int k = 0; k < n_fit; ++k)
-        for (bool rl : {false, true}) add(count_end(f, c, rl, 1 | 2 | 4));
-      add(count_end(f, c, false, 1 | 2));
-    }
-  Span sp(KC_VISIT, st, t.flops, t.bytes);
+  Count t, pad;
+  for (int c = col_lo; c <= col_hi; ++c) count_small(f, c, n_fit, &t, &pad);
+  Span sp(KC_VISIT, st, t.flops, t.bytes, pad.flops, pad.bytes);
   SmallArgs g{f, col_lo, col_hi, n_fit};
   const size_t lds = small_lds(f.K);
   const auto k = f.K <= 8    ? k_absorb_small<1, 1>

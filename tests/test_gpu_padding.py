@@ -132,3 +132,36 @@ def test_true_shape_counts_below_padded():
                                           "fit_ket", "fit_bra", "fit_local"))
     assert abs(total - sweep_flops) <= 1e-9 * sweep_flops
     ctx.set_option("timing", 0)
+
+
+@pytest.mark.parametrize("chi", [4, 8, 18])
+def test_counts_of_one_launch_columns(chi):
+    """D = 2 columns in one launch count the operations that the separate
+    launches count (precision 32 runs those; the shapes and so the counts do not
+    depend on it), QRs included, true and padded."""
+    from paper_2301_05844_amd import bbp
+    names = ("fit_visit", "fit_env", "fit_end", "fit_T1", "fit_ket", "fit_bra", "fit_local",
+             "qr")
+    got = {}
+    for precision in (64, 32):
+        ctx = bbp.BlockBP(Lx=8, Ly=8, bx=4, by=4, D=2, chi=chi)
+        ctx.set_option("precision", precision)
+        ctx.set_tensors(peps_finite(8, 8, 2, seed=2))
+        ctx.sweep(2)
+        ctx.set_option("timing", 1)
+        ctx.kernel_stats_reset()
+        ctx.sweep(1)
+        ks = {k["name"]: k for k in ctx.kernel_stats()}
+        ctx.set_option("timing", 0)
+        ctx.close()
+        got[precision] = {f: sum(ks[n][f] for n in names)
+                          for f in ("flops", "padded_flops", "bytes", "padded_bytes")}
+        if precision == 64:
+            assert ks["fit_visit"]["launches"] > 0 and ks["qr"]["launches"] == 0
+    print(got, flush=True)
+    one, many = got[64], got[32]
+    for f in ("flops", "padded_flops"):
+        assert abs(one[f] - many[f]) <= 1e-12 * many[f]
+    assert one["flops"] < one["padded_flops"] and one["bytes"] < one["padded_bytes"]
+    # T3 and most environments stay in LDS
+    assert one["bytes"] < many["bytes"] and one["padded_bytes"] < many["padded_bytes"]
