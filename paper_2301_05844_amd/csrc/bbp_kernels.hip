@@ -2724,6 +2724,8 @@ __device__ __forceinline__ double row_bcast(double x) {
 // as their DPP operand.  Broadcasts of their own (which the compiler does not
 // fold into the FMA) double a column step's FP64 instructions.  s_nop 1 covers
 // the two wait states between a VALU write of x and its DPP read.
+// The results are early-clobber operands: later instructions of a block still
+// read inputs, which may not share a register with an earlier result.
 template <int SRC>
 __device__ __forceinline__ void dot_bcast(double (&p)[4], const v4d &x) {
   asm volatile(
@@ -2732,7 +2734,7 @@ __device__ __forceinline__ void dot_bcast(double (&p)[4], const v4d &x) {
       "v_fmac_f64_dpp %1, %5, %5 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f64_dpp %2, %6, %6 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f64_dpp %3, %7, %7 row_newbcast:%8 row_mask:0xf bank_mask:0xf"
-      : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3])
+      : "+&v"(p[0]), "+&v"(p[1]), "+&v"(p[2]), "+&v"(p[3])
       : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "n"(SRC));
 }
 // x[s] += y_s bcast(g), bcast the value of lanes Q + s of the 16-lane row
@@ -2744,7 +2746,7 @@ __device__ __forceinline__ void fma_bcast4(double (&x)[4], double y0, double y1,
       "v_fmac_f64_dpp %1, %8, %5 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f64_dpp %2, %8, %6 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f64_dpp %3, %8, %7 row_newbcast:%12 row_mask:0xf bank_mask:0xf"
-      : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3])
+      : "+&v"(x[0]), "+&v"(x[1]), "+&v"(x[2]), "+&v"(x[3])
       : "v"(y0), "v"(y1), "v"(y2), "v"(y3), "v"(g), "n"(Q), "n"(Q + 1), "n"(Q + 2), "n"(Q + 3));
 }
 template <int SRC>
@@ -2756,7 +2758,7 @@ __device__ __forceinline__ void axpy_bcast(v4d &x, double c) {
       "v_fmac_f64_dpp %1, %1, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f64_dpp %2, %2, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f64_dpp %3, %3, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
-      : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3)
+      : "+&v"(x0), "+&v"(x1), "+&v"(x2), "+&v"(x3)
       : "v"(c), "n"(SRC));
   x = v4d{x0, x1, x2, x3};
 }
