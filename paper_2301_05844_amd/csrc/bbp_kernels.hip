@@ -2695,10 +2695,6 @@ __global__ __launch_bounds__(kQrgThreads) void k_qrg(QrArgs q) {
 template <int VS>
 __device__ __forceinline__ int qm_col(int c) { return c * VS + (c & 14); }
 
-__device__ __forceinline__ double join_f64(int lo, int hi) {
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
 // Sum over the four 16-lane rows: the 4x4x4 MFMA multiplies a matrix of ones
 // (row index: the lane row of the result) by x (k: the lane row), so the same
 // bits land in every row after one instruction (35 cycles) instead of two
@@ -2765,14 +2761,16 @@ __device__ __forceinline__ void axpy_bcast(v4d &x, double c) {
 
 // dlarfg's scalars from alpha and sigma^2 > 0: nrm = sqrt(alpha^2 + sigma^2),
 // beta = -sign(alpha) nrm, tau = (beta - alpha) / beta, scal = 1 / (alpha -
-// beta).  The hardware's reciprocal square root and reciprocal start a
-// third-order step each (their relative error cubed, below FP64 rounding), and
-// one residual correction rounds each result as a division or square root
-// would: panels whose columns depend on each other rely on exact values (tau
-// = 2 where sigma vanishes beside alpha).  The compiler's square root and two
-// divisions are a chain of 270 cycles on the factorisation's critical path,
-// this one of about 130.  No intermediate leaves the exponent range for a
-// finite s2, so there is no scaling.
+// beta).  The hardware's reciprocal square root and reciprocal (relative error
+// 2^-24) start a third-order step each (their error cubed, below FP64
+// rounding), and one residual correction rounds the result: over 2^21 random
+// pairs at each of several scales beta is the square root's and tau and scal
+// are the divisions' results bit for bit, from alpha^2 + sigma^2 of 2^-970 up to
+// overflow (below, the square root's residual underflows and beta is off by up
+// to 2 ulp; tau and scal are still those of that beta).  Panels whose columns
+// depend on each other rely on exact values (tau = 2 where sigma vanishes beside
+// alpha).  The compiler's square root and two divisions are a chain of 270
+// cycles on the factorisation's critical path, this one of about 130.
 struct Reflector {
   double tau, scal, beta;
 };
