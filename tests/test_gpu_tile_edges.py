@@ -95,3 +95,38 @@ def test_single_column_tile_edges(D, chi):
 @pytest.mark.parametrize("chi", [33, 36, 42, 48])
 def test_small_batch_visit_at_three_column_tiles(chi):
     _compare(4, 4, 2, chi)
+
+
+@pytest.mark.parametrize("D,H,chi", [
+    (4, 6, 48),             # 768 x 48, the largest of one workgroup
+    (4, 6, 49), (5, 5, 60), (6, 5, 54),   # 784, 1500 and 1944 rows: a workgroup per column tile
+    (6, 5, 86),             # 3096 x 86: beyond those, streamed from global memory
+])
+def test_tall_panels(D, H, chi):
+    """Columns long enough for inner panels of the full (chi D^2) x chi."""
+    _compare(D, H, 2, chi)
+
+
+@pytest.mark.parametrize("chi", [33, 48])
+def test_visit_of_three_column_tiles_at_the_smallest_bond(chi):
+    _compare(2, 6, 2, chi)
+
+
+@pytest.mark.parametrize("chi_env", [12, 16, 40])
+def test_environments_at_the_smallest_bond(chi_env):
+    """D = 2 observables: the pair-per-wave visit without a local update, at one
+    and three column tiles, against the oracle (tolerance of the observables)."""
+    from bbp_inputs import op_sz, peps_finite
+    from oracle import blockbp as ob
+    from paper_2301_05844_amd import bbp
+    kw = dict(Lx=8, Ly=8, bx=4, by=4, D=2, chi=8, chi_env=chi_env)
+    A = peps_finite(8, 8, 2, seed=7)
+    ref, g = ob.BlockBP(A, **kw), bbp.BlockBP(**kw)
+    g.set_tensors(A)
+    for _ in range(3):
+        ref.sweep()
+        g.sweep()
+    xs, ys = [0, 3, 4, 5, 7], [1, 3, 2, 6, 7]
+    sz = g.expect_sites(xs, ys, op_sz())
+    for i in range(len(xs)):
+        assert abs(sz[i] - ref.expect_site(xs[i], ys[i], op_sz())) < 1e-10
