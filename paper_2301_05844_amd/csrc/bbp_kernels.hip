@@ -651,10 +651,10 @@ struct EnvArgs {
 // that fill the CUs: four groups and, up to 32 rows (MT <= 2), two k parts;
 // from MT = 3 one, which leaves the registers for T3 two chunks ahead at MT =
 // 3.  Small batches (FILL = false), where each chunk waits for a round trip to
-// memory (2 us: T3 and Y come from other XCDs): half the columns, and two (MT
-// = 2, as LDS allows) or four times the k range a chunk.
-// One item of 32 rows 17.8 -> 13.4 us, four of 48 40.4 -> 26.7, one of 64
-// rows and 2304 columns 144 -> 88; of 16 rows it was slower (6.0 and 6.4 us).
+// memory (2 us: T3 and Y come from other XCDs): half the columns, and twice (MT
+// = 2) or four times the k range a chunk, as much as LDS holds at MT = 4.  One
+// item of 32 rows 17.8 -> 13.4 us, four of 48 40.4 -> 26.7, one of 64 rows and
+// 2304 columns 144 -> 88; of 16 rows it was slower (6.0 and 6.4 us).
 template <int MT, bool FILL = true> struct EnvShape {
   static constexpr int CG = FILL ? 4 : 2;
   static constexpr int KS = FILL ? (MT <= 2 ? 2 : 1) : 4;
@@ -4167,10 +4167,14 @@ static VisitKernel visit4_kernel(int TY, int TX) {
 static int visit4p_ne(int K) { return std::max(2, ceil16(K) / 16); }
 
 // Pair-per-wave visit (K <= 64): 2 x 2 pairs, 4 x 1 at NE = 3.  A small
-// batch at NE <= 3, whose grid would not give every CU a workgroup, takes 1 x
-// 4 pairs: two or four times the workgroups, each walking a quarter of the
-// columns xb (4 and 8 items at K = 42, 44 and 88 workgroups of 4 x 1 pairs: 83
-// -> 39 us a launch; 24 items fill the CUs with 264).
+// batch takes 1 x 4 pairs: two or four times the workgroups, each walking a
+// quarter of the columns xb.  At NE <= 2 that is a batch whose 2 x 2 grid would
+// not give every CU a workgroup.  At NE = 3 (FP64) it is one of fewer than 128
+// workgroups of 4 x 1 pairs; the two at 72 workgroups of K = 33 49 and 31 us, at
+// 96 of K = 48 65 and 39.  Launches of up to 204 gain as well (140 of K = 40 76
+// and 50, 204 of K = 48 89 and 83), 216 to 310 are about even and 360 of K = 33
+// (84 and 98) and 480 of K = 48 (119 and 159) lose; the rule sees the whole
+// batch, of which one launch may hold half, and leaves those as they are.
 template <class T>
 static bool visit4p_tiles(const FitBatch &f, int *TY, int *TX, size_t *bytes) {
   if (f.D != 4 || f.d != 2 || f.K > 64) return false;
@@ -4622,10 +4626,15 @@ hipError_t launch_inner_env(const FitBatch &f, int c, int j, bool rl, Ptr Y,
       else hipLaunchKernelGGL((k_env<4, float>), grid, dim3(EnvShape<4>::kThreads), 0, st, e);
       return hipGetLastError();
     }
-    // Fewer than 256 workgroups leave CUs idle and every chunk's round trip
-    // exposed: the shape for small batches, measured at EnvShape.
+    // The shape for small batches takes twice the workgroups and one fills a
+    // CU: up to 128 workgroups of the other a launch it is the faster one (the
+    // two in us: 120 of K = 17, D = 4 14.5 and 12.3; 120 of K = 40 33.6 and
+    // 26.2; 128 of K = 64 54 and 39), beyond the slower one (136 of K = 32 21.0
+    // and 24.0; 168 of K = 48 38.6 and 44.8; 224 of K = 64 69 and 77).  From 16
+    // messages on a shape's batch is launched in two halves by default.
     const long sel = f.tile_items > 0 ? f.tile_items : f.items;
-    if (mt > 1 && sel * grid.x < 256) {
+    const long wgs = sel * grid.x;
+    if (mt > 1 && (sel < 16 ? wgs <= 128 : wgs < 256)) {
       const dim3 half((f.K * f.P + 31) / 32, f.items);
       if (mt <= 2) hipLaunchKernelGGL((k_env<2, double, false, false>), half, dim3(EnvShape<2, false>::kThreads), 0, st, e);
       else if (mt <= 3) hipLaunchKernelGGL((k_env<3, double, false, false>), half, dim3(EnvShape<3, false>::kThreads), 0, st, e);
@@ -4713,7 +4722,10 @@ hipError_t launch_qr(const FitBatch &f, int c, int j, int mode, Ptr Y,
 
 // One launch for every visit of columns col_hi .. col_lo where the shape fits
 // k_absorb_small: D = 2, d = 2, FP64 and the LDS of one workgroup (bond caps up
-// to 20).
+// to 20), whatever the batch.  One item per CU from cap 17 on: a sweep of 8, 48,
+// 224 and 960 messages at cap 20 takes 1.4, 2.6, 2.8 and 10.0 ms, launched one
+// by one 3.5, 5.1, 14.5 and 56.6 ms; at cap 9 0.9, 1.2, 1.5 and 2.9 against 2.5,
+// 2.9, 5.7 and 20.1.
 static size_t small_lds(int K) {
   return 8 * (K <= 8    ? SmallShape<1, 1>::words(K)
               : K <= 16 ? SmallShape<1, 4>::words(K)
