@@ -1936,13 +1936,16 @@ void k_visit4p(VisitArgs v) {
 // P-long sum masks both operands when 4 does not divide P).  F is held in
 // registers (the A operand of T1, the same for every xb).
 //
-// Bound by MFMA issue on padded tiles (D = 6: 576 MFMAs a pair at K = 64, 64 %
-// of them on real entries; D = 3: 23 at K = 18).  k_visit, which the shapes
-// used before, runs the same contractions phase by phase over one workgroup
-// (six barriers a step, index decodes by division at every element).  A launch
-// there and here: the 24 to 48 messages of a D = 3, chi = 18 sweep 54.6 and
-// 19.4 us, one D = 3, chi = 15 message 24.8 and 9.9 us, one D = 6, chi = 64
-// message 1053 and 105 us (27 TFLOP/s of real entries).
+// Bound by what a wave waits for between its MFMAs, not by their rate: at D = 6,
+// K = 64 (576 MFMAs a pair, 64 % of them on real entries) the matrix cores are
+// busy 35 % of the launch, because F, T3 and accE fill all 512 registers of the
+// one wave a SIMD holds (48 more spilled) and nothing covers its LDS reads; at D
+// = 3 (23 MFMAs a pair at K = 18) a launch is a few steps long and they are busy
+// 10 %.  k_visit, which the shapes used before, runs the same contractions phase
+// by phase over one workgroup (six barriers a step, index decodes by division at
+// every element).  A launch there and here: the 24 to 48 messages of a D = 3, chi
+// = 18 sweep 54.6 and 19.4 us, one D = 3, chi = 15 message 24.8 and 9.9 us, one D
+// = 6, chi = 64 message 1053 and 105 us (27 TFLOP/s of real entries).
 //
 // Tiles: TX = 4 pairs along xb of one yf (TY = 1) where four X and G tiles
 // fit in LDS (D <= 3; D = 5, 6 up to 32 rows), so that a single message still
