@@ -2843,7 +2843,9 @@ __device__ __forceinline__ void qm_reduce(const v4d &acc, double (*wred)[256], d
 // panels have rows or columns that are exactly zero (single-layer networks,
 // trivial legs), which Q keeps only where T agrees with V bit for bit; the
 // leftovers of 1e-16 would otherwise be normalised to full columns by the next
-// site's factorisation.
+// site's factorisation.  Columns that vanish only to rounding level are not
+// covered: what such a fit converges to depends on rounding with either form of
+// T, as it does in LAPACK.
 //
 // Bound by the instructions of a step, about 100 of them beside the tiles'
 // own, which every wave issues for itself, and by their dependent chain (one
