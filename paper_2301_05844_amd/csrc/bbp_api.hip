@@ -1353,6 +1353,34 @@ static uint64_t region_slot(int kind, int bi, int bj, char orient) {
          ((uint64_t)bi << 12) | ((uint64_t)dir_index(orient) << 8);
 }
 
+// Boundary stacks of Wc columns of Hc sites, lines of Hc sites and their
+// matrix-unit steps that the regions of every site and bond of the lattice
+// have together.  Kernel variants that differ in rounding are chosen by these
+// and not by the regions of one call: a value does not depend on what else is
+// contracted with it (bbp_expect_terms gives the bits of the separate calls).
+struct RegionCounts {
+  int stacks = 0, lines = 0, units = 0;
+};
+static RegionCounts lattice_counts(const bbp_ctx *c, int Wc, int Hc) {
+  const int d2 = c->d * c->d, bx = c->bx, by = c->by, blocks = c->gx * c->gy;
+  const int right = c->infinite ? 1 : (c->gx - 1) * c->gy;
+  const int down = c->infinite ? 1 : c->gx * (c->gy - 1);
+  RegionCounts n;
+  // a frame of `count` regions: two stacks of w x h and w lines each, on a line
+  // `at` sites (or first sites of bonds)
+  auto frame = [&](int count, int w, int h, int at) {
+    if (h != Hc) return;
+    if (w == Wc) n.stacks += 2 * count;
+    n.lines += count * w;
+    n.units += count * w * at * d2;
+  };
+  frame(blocks, by, bx, bx);      // blocks, row frame
+  frame(blocks, bx, by, by - 1);  // blocks, column frame
+  frame(right, by, 2 * bx, 1);    // two blocks side by side: the bond across
+  frame(down, bx, 2 * by, 1);     // two blocks, one above the other
+  return n;
+}
+
 // Gather table and bond lists of one rotated side made of message segments.
 static void side_source(const bbp_ctx *c, const std::vector<Seg> &segs,
                         bool rev, GatherSrc &g, int k, std::vector<int> &bonds) {
@@ -1479,8 +1507,11 @@ static bbp_status compute_regions(bbp_ctx *c, std::vector<RegionSpec> &regs) {
   std::map<std::pair<int, int>, std::vector<int>> sgroups;
   for (size_t i = 0; i < stacks.size(); ++i)
     if (!reused[i]) sgroups[{stacks[i].Wc, stacks[i].Hc}].push_back((int)i);
+  // every line of its regions, or only those of the listed bonds
+  const bool whole = std::all_of(regs.begin(), regs.end(),
+                                 [](const RegionSpec &R) { return R.targets.empty(); });
   std::vector<std::vector<int>> batches;
-  std::vector<int> shape_items;  // items of the shape each batch belongs to
+  std::vector<int> shape_items;  // items the kernels of each batch are chosen for
   std::vector<int> batch_lane;
   if (reuse) {  // kept stacks are updated in place, one per batch
     for (auto &kv : sgroups)
@@ -1516,8 +1547,10 @@ static bbp_status compute_regions(bbp_ctx *c, std::vector<RegionSpec> &regs) {
     std::vector<double> cost;
     for (const Shape &sh : shapes)
       for (auto &part : split_batch(*sh.ids, sh.parts, kLaneMinItems)) {
+        const StackItem &it = stacks[part[0]];
         batches.push_back(part);
-        shape_items.push_back((int)sh.ids->size());
+        shape_items.push_back(whole ? lattice_counts(c, it.Wc, it.Hc).stacks
+                                    : (int)sh.ids->size());
         cost.push_back(sh.cost);
       }
     std::vector<int> order(batches.size());
@@ -1702,6 +1735,8 @@ static bbp_status compute_regions(bbp_ctx *c, std::vector<RegionSpec> &regs) {
                                 true);
     if (bs != BBP_OK) return bs;
     FitBatch &f = lg.fb;
+    const RegionCounts all = lattice_counts(c, 1, Hc);
+    if (whole) f.tile_items = all.lines;
     pl.lane = std::max(0, stack_lane[lines[lids[0]].xs]);
     // the left and right environment chains are independent: the right one
     // takes a lane of its own (with a T3 scratch of its own) where the visit
@@ -1782,6 +1817,7 @@ static bbp_status compute_regions(bbp_ctx *c, std::vector<RegionSpec> &regs) {
       bbp_status bs2 = alloc_batch(c, *pl.ug, (int)chmax, Kenv,
                                    std::vector<uint64_t>(chmax, 0), NEED_SCRATCH, true);
       if (bs2 != BBP_OK) return bs2;
+      if (whole) pl.ug->fb.tile_items = std::min(256, all.units);
     }
   }
 

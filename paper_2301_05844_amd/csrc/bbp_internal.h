@@ -50,8 +50,10 @@ __host__ __device__ inline SiteExt site_ext(const FitDims &d, int j, int N, bool
 // first K*K doubles of their slot as a [phys][bond] or [bond][phys] matrix.
 struct FitBatch {
   int items = 0;
-  // items the visit's tiling is chosen for: the whole batch's count where a
-  // batch is split over streams, so that every part runs the same kernels
+  // items the visit's tiling and the environment update's shape are chosen for:
+  // the whole batch's count where a batch is split over streams, the whole
+  // lattice's in the observables, a fixed one where requests share a batch, so
+  // that an item's kernels do not depend on what it is launched with
   int tile_items = 0;
   int K = 0, P = 0, D = 0, d = 0;  // bond cap, D^2, D, physical dim
   int H = 0, W = 0, N = 0;          // column height, width, N = H + 2

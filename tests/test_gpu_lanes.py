@@ -98,3 +98,35 @@ def test_expect_terms_bitwise_equal(lanes):
     assert np.array_equal(s3, sz[:5]) and b3.size == 0
     s4, b4 = tog.expect_terms([], [], op_sz(), bonds[:7], op_heis())
     assert s4.size == 0 and np.array_equal(b4, ss[:7])
+
+
+@pytest.mark.parametrize("L,bx,by,D,chi,chi_env", [
+    (8, 4, 4, 4, 8, 42), (8, 4, 4, 4, 8, 28), (8, 2, 2, 3, 9, 28), (6, 3, 3, 5, 8, 36),
+    (8, 2, 4, 3, 9, 18),   # lines of four sites from blocks and from unions
+])
+def test_expect_terms_of_unequal_regions(L, bx, by, D, chi, chi_env):
+    """The sites of one block and the bonds of all of them from one call: the
+    regions contracted together outnumber those of the sites alone, and every
+    value is still bitwise that of the two separate calls; so are values asked
+    for one by one."""
+    from paper_2301_05844_amd import bbp
+    A = peps_finite(L, L, D, seed=3)
+    kw = dict(Lx=L, Ly=L, bx=bx, by=by, D=D, chi=chi, chi_env=chi_env)
+    xs = np.array([L - 1 - x for y in range(by) for x in range(bx)], dtype=np.int32)
+    ys = np.array([L - 1 - y for y in range(by) for x in range(bx)], dtype=np.int32)
+    bonds = [(x, y, x + 1, y) for y in range(L) for x in range(L - 1)]
+    bonds += [(x, y, x, y + 1) for y in range(L - 1) for x in range(L)]
+    print(f"case {kw}", flush=True)
+
+    def ctx():
+        c = bbp.BlockBP(**kw)
+        c.set_tensors(A)
+        c.sweep(2)
+        return c
+
+    sz, ss = ctx().expect_terms(xs, ys, op_sz(), bonds, op_heis())
+    assert np.array_equal(ctx().expect_sites(xs, ys, op_sz()), sz)
+    assert np.array_equal(ctx().expect_bonds(bonds, op_heis()), ss)
+    one = ctx()
+    for i in (0, len(bonds) // 2, len(bonds) - 1):
+        assert np.array_equal(one.expect_bonds(bonds[i:i + 1], op_heis()), ss[i:i + 1])
