@@ -726,7 +726,7 @@ def svd_bench(args):
         sweeps=dict(mean=float(np.mean(sweeps)), max=int(np.max(sweeps))),
         max_rel_err_singular_values_vs_oracle=err,
         roofline=dict(bound="alu", achieved=achieved, peak=78.6, unit="TFLOP/s",
-                      frac=achieved / 78.6, traffic=None, kernel="k_svd_jacobi",
+                      frac=achieved / 78.6, traffic=None, kernel="k_svd_reg",
                       avg_us=ev_ms * 1e3, flops_per_launch=flops,
                       counted_on="pair sums of every sweep each item took, rotations of "
                                  "every pair of every sweep but the last (an upper bound)"),
