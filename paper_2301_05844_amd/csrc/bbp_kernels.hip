@@ -986,6 +986,9 @@ struct VisitArgs {
   // true extents of site j of column c (null: the full bond cap K); only
   // the pair-per-wave D = 4 kernel uses them to skip zero padding
   const FitDims *dims;
+  // where the padding is run all the same: the true extents that the same
+  // kernel's sums are ordered by (null: the full bond cap)
+  const FitDims *order;
   int W, c, j, N;
   Ptr F, X, G, Y;
   const double *aket;
@@ -1691,6 +1694,10 @@ void k_visit4p(VisitArgs v) {
     return;
   }
   const int K4x = ceil4(nxf), tnb = ceil16(nyb) >> 4;
+  // T1 sums whole blocks of 16 xf in two chains and the rest in one: cut at the
+  // true X bond also where the padding is run, so that both sum alike
+  int K4s = K4x;
+  if (v.order) K4s = ceil4(site_ext(v.order[(size_t)it * v.W + v.c], v.j, v.N, v.rl != 0).xf);
   T *Fs = sm;
   T *Xs = Fs + TY * 16 * FS;
   T *T13s = Xs + TX * XT;
@@ -1800,7 +1807,7 @@ void k_visit4p(VisitArgs v) {
       // Xs row xf = k0 + lq (k0 = 0 mod 4): swizzle ((k0 >> 1) & 15) ^ (lq >> 1)
       const int xb0 = lq * 16 + (lr ^ (lq >> 1));
       int k0 = 0;
-      for (; k0 + 16 <= K4x; k0 += 16) {
+      for (; k0 + 16 <= K4s; k0 += 16) {
         const T *pk = px + k0 * 16;
         const int sw = (k0 >> 1) & 8;
         T av[4], bv[4];
@@ -4416,7 +4423,7 @@ static hipError_t launch_fused(const FitBatch &f, int c, int j, bool rl, Ptr X,
   v.abra_stride = f.bra_one ? 0 : a_stride(f);
   v.t3 = f.t3;
   v.t3_stride = t1_stride(f);
-  v.dims = nullptr;
+  v.dims = v.order = nullptr;
   v.W = f.W; v.c = c; v.j = j; v.N = f.N;
   const double it = f.items, K = f.K, P = f.P, d = f.d;
   double flops = it * (2 * K * K * K * P * P + 4 * d * K * K * P * P * P);
@@ -4434,7 +4441,7 @@ static hipError_t launch_fused(const FitBatch &f, int c, int j, bool rl, Ptr X,
   if (pairw) {  // one (yf, xb) pair per wave; skips the zero padding
     v.TY = TYp;
     v.TX = TXp;
-    v.dims = f.bounded && f.hdims ? f.dims : nullptr;
+    (f.bounded ? v.dims : v.order) = f.hdims ? f.dims : nullptr;
     const int ne = visit4p_ne(f.K);
     hipLaunchKernelGGL(f32 ? visit4p_kernel<float>(ne, TYp) : visit4p_kernel<double>(ne, TYp),
                        dim3((f.K + TYp - 1) / TYp, f.items), dim3(64 * TYp * TXp), ldsp, st, v);

@@ -90,6 +90,25 @@ def test_skip_padding_bitwise_other_bond_dimensions(case):
     assert np.array_equal(a[2], b[2]) and np.array_equal(a[3], b[3])
 
 
+# Caps of more whole blocks of 16 X bonds than the true bonds fill: the D = 4
+# visit sums whole blocks in two chains and the rest in one.
+@pytest.mark.parametrize("precision,seed,kw", [
+    (64, 178, dict(Lx=7, Ly=8, bx=2, by=4, D=4, chi=22, chi_env=29)),
+    (64, 113, dict(Lx=9, Ly=13, bx=4, by=4, D=4, chi=12, chi_env=21)),
+    (64, 72, dict(Lx=15, Ly=8, bx=4, by=2, D=4, chi=44, chi_env=53)),
+    (32, 28, dict(Lx=11, Ly=5, bx=4, by=3, D=4, chi=41, chi_env=48)),
+])
+def test_skip_padding_bitwise_where_blocks_end_at_the_true_bond(precision, seed, kw):
+    A = peps_finite(kw["Lx"], kw["Ly"], 4, seed=seed)
+    print(f"case {kw}", flush=True)
+    a = _solve(0, A, 3, precision=precision, **kw)
+    b = _solve(1, A, 3, precision=precision, **kw)
+    assert np.array_equal(a[0], b[0])
+    for ma, mb in zip(a[1], b[1]):
+        assert np.array_equal(ma, mb)
+    assert np.array_equal(a[2], b[2]) and np.array_equal(a[3], b[3])
+
+
 @pytest.mark.parametrize("precision,graphs", [(32, 1), (64, 0)])
 def test_skip_padding_bitwise_fp32_and_eager(precision, graphs):
     kw = dict(Lx=8, Ly=12, bx=4, by=4, D=4, chi=32, chi_env=42)
